@@ -184,19 +184,19 @@ __global__ void dilate_kernel(const int8_t *in, int8_t *out, int nbx, int nby, i
     out[i] = (int8_t)best;
 }
 
-// Block maxima and flags of a row-tile sensor step from the max bits its
-// workgroups folded into the low halves of the accumulator words, which are
+// Block maxima and flags of a sensor step whose workgroups folded max bits
+// into per-block words (words[b * stride], as values of type C), which are
 // cleared for the next sensor step; the L2 sensor's square root is taken
 // here, once per block.
 template <typename C>
-__global__ void finish_blocks_kernel(unsigned *w32, int nblocks, bool l2, C *block_max, int8_t *flags,
+__global__ void finish_blocks_kernel(C *words, int stride, int nblocks, bool l2, C *block_max, int8_t *flags,
                                      double theta_r, double theta_c) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= nblocks) return;
-    float M = __uint_as_float(w32[2 * b]);
-    w32[2 * b] = 0u;
-    if (l2) M = sqrtf(M);
-    block_max[b] = static_cast<C>(M);
+    C M = words[(int64_t)b * stride];
+    words[(int64_t)b * stride] = C(0);
+    if (l2) M = sqrt(M);
+    block_max[b] = M;
     flags[b] = block_flag(static_cast<double>(M), theta_r, theta_c);
 }
 

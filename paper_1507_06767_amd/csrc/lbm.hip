@@ -242,8 +242,7 @@ namespace {
 // Streaming scheme: in place (one buffer, the AA pattern) when a buffer is at
 // most 512 MiB, so that the working set of a step can stay in the Infinity
 // Cache; ping-pong above, where the two are on par and ping-pong streams its
-// stores non-temporally.  3D float64 always uses ping-pong (its z-march
-// kernel).  An explicit choice in the descriptor wins; under
+// stores non-temporally.  3D float64 always uses ping-pong.  An explicit choice in the descriptor wins; under
 // LBM_STREAMING_AUTO the environment variable LBM_STREAMING=pingpong|inplace
 // overrides the size rule (tests run both schemes that way).
 bool multi_setting(const lbm_desc *d, const Layout &L);
@@ -298,11 +297,9 @@ Planes<T> planes_of(lbm_blocks *h, void *buf) {
 }
 
 template <int Q, typename C>
-StepArgs<C> step_args(lbm_blocks *h, const void *src, void *dst, bool zmarch, int tile_x) {
+StepArgs<C> step_args(lbm_blocks *h, const void *src, void *dst, int tile_x) {
     StepArgs<C> a{};
     const lbm_desc &d = h->d;
-    constexpr int D = Lattice<Q>::D;
-    const int BZ = (D == 3) ? kBlockEdge : 1;
     a.src = src;
     a.dst = dst;
     a.pitch = (uint32_t)h->L.pitch;
@@ -311,8 +308,7 @@ StepArgs<C> step_args(lbm_blocks *h, const void *src, void *dst, bool zmarch, in
     a.nz = d.extent[2];
     a.ntx = (a.nx + tile_x - 1) / tile_x;
     a.nty = (a.ny + tile_rows(tile_x) - 1) / tile_rows(tile_x);
-    const int ntz = zmarch ? (a.nz + BZ - 1) / BZ : a.nz;
-    a.ntiles = a.ntx * a.nty * ntz;
+    a.ntiles = a.ntx * a.nty * a.nz;
     a.nbx = h->L.nb[0];
     a.nby = h->L.nb[1];
     a.wall = h->wall_mask;
@@ -377,17 +373,15 @@ void reset_accumulators(lbm_blocks *h) {
                        acc, (int)h->L.nblocks);
 }
 
-// Row tiles leave a sensor step's block maxima as max bits in the
-// accumulator words: the block maxima and flags are written from them right
-// after the step (and the words cleared).
+// Row tiles and 3D float64 leave a sensor step's block maxima as max bits in
+// the accumulator words (a float's in the low half): the block maxima and
+// flags are written from them right after the step (and the words cleared).
+template <typename C>
 void finish_blocks(lbm_blocks *h) {
-    auto *w32 = reinterpret_cast<unsigned *>(static_cast<char *>(h->d.buf[LBM_BUF_BLOCK_MAX]) + h->L.acc_off);
-    const bool l2 = h->d.sensor_kind == LBM_SENSOR_L2;
-    auto *fl = static_cast<int8_t *>(h->d.buf[LBM_BUF_FLAGS]);
-    const unsigned g = grid_for(h->L.nblocks);
-    // float storages only: 3D float64 steps with the z-march kernel
-    hipLaunchKernelGGL(finish_blocks_kernel<float>, dim3(g), dim3(kAuxThreads), 0, h->stream, w32,
-                       (int)h->L.nblocks, l2, static_cast<float *>(h->d.buf[LBM_BUF_BLOCK_MAX]), fl,
+    auto *words = reinterpret_cast<C *>(static_cast<char *>(h->d.buf[LBM_BUF_BLOCK_MAX]) + h->L.acc_off);
+    hipLaunchKernelGGL(finish_blocks_kernel<C>, dim3(grid_for(h->L.nblocks)), dim3(kAuxThreads), 0, h->stream, words,
+                       (int)(8 / sizeof(C)), (int)h->L.nblocks, h->d.sensor_kind == LBM_SENSOR_L2,
+                       static_cast<C *>(h->d.buf[LBM_BUF_BLOCK_MAX]), static_cast<int8_t *>(h->d.buf[LBM_BUF_FLAGS]),
                        h->d.theta_refine, h->d.theta_coarsen);
 }
 
@@ -402,11 +396,11 @@ void launch_step(lbm_blocks *h, bool sens) {
     c.sensor_kind = h->d.sensor_kind;
     c.force = h->has_force;
     c.smag = h->d.smagorinsky > 0.0;
-    constexpr bool zm = uses_zmarch<Q, C>();
-    c.tile_x = zm ? 64 : h->tile_x;
-    const StepArgs<C> a = step_args<Q, C>(h, src, dst, zm, c.tile_x);
+    c.tile_x = h->tile_x;
+    const StepArgs<C> a = step_args<Q, C>(h, src, dst, c.tile_x);
     launch_step_kernel<Q, T, C, SH>(a, c);
-    if (sens && c.tile_x == kRowTileX && c.scheme == kPingPong) finish_blocks(h);
+    const bool folded = sizeof(C) == 8 ? h->L.dim == 3 : c.tile_x == kRowTileX && c.scheme == kPingPong;
+    if (sens && folded) finish_blocks<C>(h);
 }
 
 // Where host data and initial states are written: the state buffer for
@@ -438,7 +432,7 @@ void *canonical_state(lbm_blocks *h) {
                                (int)h->L.cells);
         } else {
             using C = std::conditional_t<sizeof(T) == 8, double, float>;
-            const StepArgs<C> a = step_args<Q, C>(h, A, B, false, h->tile_x);
+            const StepArgs<C> a = step_args<Q, C>(h, A, B, h->tile_x);
             hipLaunchKernelGGL((unstream_kernel<Q, T, C>), dim3(grid_for(h->L.cells)), dim3(kAuxThreads), 0,
                                h->stream, a, static_cast<T *>(B));
         }
@@ -475,7 +469,7 @@ void launch_multi(lbm_blocks *h, int m) {
     c.sensor_kind = h->d.sensor_kind;
     c.force = h->has_force;
     c.smag = h->d.smagorinsky > 0.0;
-    const StepArgs<C> a = step_args<9, C>(h, state_ptr(h), h->d.buf[h->cur ? LBM_BUF_F_A : LBM_BUF_F_B], false,
+    const StepArgs<C> a = step_args<9, C>(h, state_ptr(h), h->d.buf[h->cur ? LBM_BUF_F_A : LBM_BUF_F_B],
                                           h->tile_x);
     launch_multi_kernel<9, T, C, SH>(a, m, c);
 }
@@ -605,7 +599,7 @@ lbm_status lbm_create_blocks(const lbm_desc *d, const double *f0_host, lbm_block
     h->L = L;
     h->stream = static_cast<hipStream_t>(d->stream);
     h->inplace = inplace_setting(d, L);
-    // 3D float64 has one tile shape (the z-march kernel, 64 x 8)
+    // 3D float64 has one tile shape (64 x 8)
     h->tile_x = (L.dim == 3 && d->storage == LBM_F64) ? 64 : tile_x_setting(d->extent[0], h->inplace, L.dim);
     h->phase = 0;
     h->cur = 0;
@@ -1022,8 +1016,7 @@ lbm_status lbm_autotune(lbm_blocks *h, int32_t reps, int32_t *tile_x) {
     lbm_status st = check_handle(h);
     if (st != LBM_OK) return st;
     if (reps < 1) return fail(LBM_EINVAL, "reps = %d < 1", reps);
-    const bool zm = h->d.lattice != LBM_D2Q9 && h->d.storage == LBM_F64;
-    if (zm) {   // the z-march kernel has one tile shape
+    if (h->d.lattice != LBM_D2Q9 && h->d.storage == LBM_F64) {   // one tile shape
         if (tile_x) *tile_x = 64;
         return LBM_OK;
     }

@@ -31,21 +31,18 @@
 //    state (152 MiB) then stays in the 256 MB Infinity Cache.  Bounce-back
 //    folds into the addressing of both halves of kStream.
 //
-// Two work decompositions:
-//  * step_cells: one cell per thread; a workgroup is BX x 8 cells of one
-//    z-slice, i.e. BX/8 block columns of one 8x8 block row.  The workgroup
-//    reduces its part of each block maximum with 8-lane shuffles and one LDS
-//    exchange; in 2D that is the whole block.  In 3D the 8 z-slices of a block
-//    are combined through one 64-bit word per block holding (arrival count <<
-//    32 | max bits): each contributor folds its value in with a
-//    compare-and-swap, and the one that completes the count writes the block
-//    maximum and flag and clears the word for the next sensor step.  The max
-//    is order independent, so the result is deterministic.  Used for float
-//    storage (a float's bits fit beside the count).
-//  * step_zmarch: one thread marches over the 8 z-slices of a block column, so
-//    a BX x 8 workgroup holds whole 8x8x8 blocks and finishes their maxima
-//    itself.  Used for 3D float64 storage, whose 64-bit maximum leaves no room
-//    for a count.
+// Work decomposition (step_cells): one cell per thread; a workgroup is BX x 8
+// cells of one z-slice, i.e. BX/8 block columns of one 8x8 block row.  The
+// workgroup reduces its part of each block maximum with 8-lane shuffles and
+// one LDS exchange; in 2D that is the whole block.  In 3D the 8 z-slices of a
+// block are combined through one 64-bit word per block.  In float it holds
+// (arrival count << 32 | max bits): each contributor folds its value in with a
+// compare-and-swap, and the one that completes the count writes the block
+// maximum and flag and clears the word for the next sensor step.  A float64
+// maximum leaves no room for the count: each contributor folds its bits in
+// with one atomic max, and finish_blocks_kernel, launched right after, writes
+// the block maxima and flags (as for row tiles).  The max is order
+// independent, so the result is deterministic.
 //
 // Arithmetic is done on the shifted populations d_i = f_i - w_i rho0, which
 // keeps the float32 variants accurate: every quantity the sensor and the
@@ -104,7 +101,7 @@ struct StepArgs {
     C *block_max;           // [nbz][nby][nbx]
     int8_t *flags;          // [nbz][nby][nbx]
     unsigned long long *acc;  // per block (count << 32 | max bits), zero between steps; row tiles
-                              // fold max bits into its low 32-bit half
+                              // fold max bits into its low 32-bit half, 3D float64 into the word
 };
 
 // Workgroups are dealt to the 8 XCDs round-robin by workgroup id.  Renumber
@@ -642,7 +639,6 @@ template <int Q, typename T, typename C, bool SHIFTED, bool SENSOR, int SKIND, i
 __global__ __launch_bounds__(BX *TY) void step_cells(const StepArgs<C> a) {
     constexpr int D = Lattice<Q>::D;
     static_assert(BX % kBlockEdge == 0, "tile width must hold whole blocks");
-    static_assert(D == 2 || !SENSOR || sizeof(C) == 4, "3D float64 uses step_zmarch");
     static_assert(TY == kTileY || (D == 3 && kTileY % TY == 0), "row tiles are for 3D grids");
 
     const int tile = (TY == kTileY) ? xcd_tile(blockIdx.x, a.ntiles) : (int)blockIdx.x;
@@ -674,6 +670,14 @@ __global__ __launch_bounds__(BX *TY) void step_cells(const StepArgs<C> a) {
                     const int b = (bz * a.nby + by) * a.nbx + bx;
                     // M >= 0, +inf or NaN: unsigned order of the bits is a
                     // NaN-propagating max order
+                    if constexpr (sizeof(C) == 8) {
+                        // (a march of each workgroup over the block's 8 slices, which
+                        // needs no atomic, took 80 us on a 96^3 D3Q19 grid: 8 times
+                        // fewer workgroups, too few to fill the chip)
+                        __hip_atomic_fetch_max(&a.acc[b], __builtin_bit_cast(unsigned long long, M), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                        return;
+                    }
                     const unsigned mine = __float_as_uint(static_cast<float>(M));
                     if constexpr (TY < kTileY) {
                         // Row tiles: 64 workgroups meet in a block, most of them at
@@ -702,42 +706,6 @@ __global__ __launch_bounds__(BX *TY) void step_cells(const StepArgs<C> a) {
                     if (cnt == need) write_block(a, b, finish<SKIND>(static_cast<C>(__uint_as_float(top))));
                 }
             }
-        }
-    }
-}
-
-template <int Q, typename T, typename C, bool SHIFTED, bool SENSOR, int SKIND, int MODEL, int BX>
-__global__ __launch_bounds__(BX *kTileY) void step_zmarch(const StepArgs<C> a) {
-    static_assert(Lattice<Q>::D == 3, "z-march is for 3D grids");
-    const int tile = xcd_tile(blockIdx.x, a.ntiles);
-    const int tix = tile % a.ntx;
-    const int rest = tile / a.ntx;
-    const int tiy = rest % a.nty;
-    const int tiz = rest / a.nty;
-    const int x = tix * BX + (int)threadIdx.x;
-    const int y = tiy * kTileY + wave_row<BX>();
-    const int z0 = tiz * kBlockEdge;
-
-    C m = C(0);
-    if (x < a.nx && y < a.ny) {
-        const int zend = min(z0 + kBlockEdge, a.nz);
-#pragma unroll 1
-        for (int z = z0; z < zend; ++z) {
-            const Geo<C> g = make_geo<3>(a, x, y, z);
-            C d[Q];
-            load_cell<Q, T, C, SHIFTED, kPingPong>(a, g, d);
-            const C s = collide_store<Q, T, C, SHIFTED, SENSOR, SKIND, MODEL, kPingPong>(a, g, d);
-            if constexpr (SENSOR) {
-                m = nan_max(m, s);
-                accumulate<SKIND>(a, g.cell, s);
-            }
-        }
-    }
-    if constexpr (SENSOR) {
-        const C M = tile_block_max<BX, kTileY>(m);
-        if (threadIdx.y == 0 && threadIdx.x < BX / kBlockEdge) {
-            const int bx = tix * (BX / kBlockEdge) + (int)threadIdx.x;
-            if (bx < a.nbx) write_block(a, (tiz * a.nby + tiy) * a.nbx + bx, finish<SKIND>(M));
         }
     }
 }
