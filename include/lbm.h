@@ -153,8 +153,9 @@ typedef struct {
  * buf_bytes fields are ignored).  Pure host computation, no HIP call.
  *   F_A, F_B   : two population arrays of q padded planes each.  Ping-pong
  *                streaming alternates between them; the in-place scheme
- *                (chosen for arrays up to 512 MiB) steps F_A only and uses F_B
- *                as staging when states are read or written;
+ *                (chosen for arrays up to 512 MiB) steps one of them and uses
+ *                the other as staging when states are read or written, and a
+ *                launch of two steps moves the state from one to the other;
  *   BLOCK_MAX  : one float32 (float32/16-bit storages) or float64 (F64) per block,
  *                followed by one 64-bit accumulator word per block;
  *   FLAGS      : one int8 per sensor block;
@@ -172,6 +173,8 @@ lbm_status lbm_create_blocks(const lbm_desc *d, const double *f0_host, lbm_block
 /* Enqueues n >= 0 steps k = s+1 .. s+n, s being the current step counter.
  * Step k also evaluates the sensor, its block maxima and the flags when
  * sensor_every > 0 and k % sensor_every == 0 (sensor_every == 0: never).
+ * Two steps of a 3D float32 or float64 grid may share one launch where that
+ * is the faster form; results are identical bit for bit.
  * Asynchronous: returns once the launches are enqueued. */
 lbm_status lbm_step_n(lbm_blocks *h, int64_t n, int32_t sensor_every);
 

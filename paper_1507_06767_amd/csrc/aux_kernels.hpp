@@ -186,15 +186,17 @@ __global__ void dilate_kernel(const int8_t *in, int8_t *out, int nbx, int nby, i
 
 // Block maxima and flags of a sensor step whose workgroups folded max bits
 // into per-block words (words[b * stride], as values of type C), which are
-// cleared for the next sensor step; the L2 sensor's square root is taken
-// here, once per block.
+// cleared for the next sensor step, as are those of the other step of a pair
+// (other; nullptr: none); the L2 sensor's square root is taken here, once per
+// block.
 template <typename C>
-__global__ void finish_blocks_kernel(C *words, int stride, int nblocks, bool l2, C *block_max, int8_t *flags,
+__global__ void finish_blocks_kernel(C *words, C *other, int stride, int nblocks, bool l2, C *block_max, int8_t *flags,
                                      double theta_r, double theta_c) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= nblocks) return;
     C M = words[(int64_t)b * stride];
     words[(int64_t)b * stride] = C(0);
+    if (other) other[(int64_t)b * stride] = C(0);
     if (l2) M = sqrt(M);
     block_max[b] = M;
     flags[b] = block_flag(static_cast<double>(M), theta_r, theta_c);

@@ -8,6 +8,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "pair_kernel.hpp"
 #include "step_kernel.hpp"
 
 namespace lbm {
@@ -32,6 +33,13 @@ void launch_step_kernel(const StepArgs<C> &a, const LaunchCfg &c);
 // and stochastic rounding, which the host never sends here.
 template <int Q, typename T, typename C, bool SH>
 void launch_multi_kernel(const StepArgs<C> &a, int nsteps, const LaunchCfg &c);
+
+// Enqueues two steps of a 3D grid as one step_pair launch (a.src -> a.dst;
+// scheme kStream: both buffers in the slot order of the in-place scheme); a
+// no-op where pair_supported is false, which the host never sends here.
+// c.sensor: either step evaluates the sensor (p.sensor says which).
+template <int Q, typename T, typename C, bool SH>
+void launch_pair_kernel(const StepArgs<C> &a, const PairArgs &p, const LaunchCfg &c);
 
 #ifdef LBM_LAUNCH_DEFINITIONS
 template <int Q, typename T, typename C, bool SH, bool SENS, int SK, int MODEL, int BX, int SCH>
@@ -90,6 +98,36 @@ void launch_multi_kernel(const StepArgs<C> &a, int nsteps, const LaunchCfg &c) {
     } else {
         (void)a, (void)nsteps, (void)c;
     }
+}
+
+template <int Q, typename T, typename C, bool SH, bool SENS, int SK, int MODEL>
+void launch_pair_one(const StepArgs<C> &a, const PairArgs &p, const LaunchCfg &c) {
+    if constexpr (pair_supported<Q, T, MODEL>()) {
+        const dim3 g(p.ntiles), b(pair_threads<Q, T>());
+        if constexpr (sizeof(T) == 4) {   // 3D float64 is never in place
+            if (c.scheme == kStream) {
+                hipLaunchKernelGGL((step_pair<Q, T, C, SH, SENS, SK, MODEL, true>), g, b, 0, c.stream, a, p);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((step_pair<Q, T, C, SH, SENS, SK, MODEL, false>), g, b, 0, c.stream, a, p);
+    } else {
+        (void)a, (void)p, (void)c;
+    }
+}
+
+template <int Q, typename T, typename C, bool SH, bool SENS, int SK>
+void launch_pair_model(const StepArgs<C> &a, const PairArgs &p, const LaunchCfg &c) {
+    if (c.force) launch_pair_one<Q, T, C, SH, SENS, SK, kModelForce>(a, p, c);
+    else if (c.smag) launch_pair_one<Q, T, C, SH, SENS, SK, kModelSmag>(a, p, c);
+    else launch_pair_one<Q, T, C, SH, SENS, SK, 0>(a, p, c);
+}
+
+template <int Q, typename T, typename C, bool SH>
+void launch_pair_kernel(const StepArgs<C> &a, const PairArgs &p, const LaunchCfg &c) {
+    if (!c.sensor) launch_pair_model<Q, T, C, SH, false, kSensorL2>(a, p, c);
+    else if (c.sensor_kind == kSensorL2) launch_pair_model<Q, T, C, SH, true, kSensorL2>(a, p, c);
+    else launch_pair_model<Q, T, C, SH, true, kSensorKKn>(a, p, c);
 }
 
 template <int Q, typename T, typename C, bool SH>

@@ -231,8 +231,12 @@ struct lbm_blocks {
     uint32_t wall_mask;
     int multi;                // most sensor-free steps per step_multi launch (small 2D
                               // ping-pong grids), 0: one launch per step
+    bool pair_sensor, pair_plain;   // two steps are taken by one step_pair launch: with the
+                                    // sensor at either of them, without it
+    PairArgs pair_args;       // its tiles (the sensor words are filled in per launch)
+    int flip;                 // in place: 1 while the caller's F_A and F_B have changed roles
     int graph_chunk;          // steps per graph replay (even), 0: launch step by step
-    hipGraphExec_t graph[2];  // graph_chunk steps, by buffer parity
+    hipGraphExec_t graph[4];  // graph_chunk steps, by buffer parity and flip
     std::vector<int8_t> flags_host;
     std::vector<unsigned char> bmax_host;
 };
@@ -364,6 +368,16 @@ void with_types(lbm_blocks *h, F &&f) {
 
 unsigned grid_for(int64_t n) { return (unsigned)((n + kAuxThreads - 1) / kAuxThreads); }
 
+// Words that a pair's sensors are folded into (zero between steps): float
+// storages use the halves of the blocks' accumulator words, float64 the words
+// for the first step and the averaged sensor's maxima in the scratch buffer
+// for the second, which are cleared here.
+void clear_second_words(lbm_blocks *h) {
+    if (h->L.dim != 3 || h->L.cbytes != 8) return;
+    hipLaunchKernelGGL(zero_words_kernel, dim3(grid_for(h->L.nblocks)), dim3(kAuxThreads), 0, h->stream,
+                       reinterpret_cast<unsigned long long *>(scratch_d(h, h->L.avgmax_off)), (int)h->L.nblocks);
+}
+
 // The step kernel's per-block (count | max) words must read zero before a
 // sensor step; they are cleared whenever a state is installed.
 void reset_accumulators(lbm_blocks *h) {
@@ -371,16 +385,25 @@ void reset_accumulators(lbm_blocks *h) {
                                                        h->L.acc_off);
     hipLaunchKernelGGL(zero_words_kernel, dim3(grid_for(h->L.nblocks)), dim3(kAuxThreads), 0, h->stream,
                        acc, (int)h->L.nblocks);
+    clear_second_words(h);
 }
 
-// Row tiles and 3D float64 leave a sensor step's block maxima as max bits in
-// the accumulator words (a float's in the low half): the block maxima and
-// flags are written from them right after the step (and the words cleared).
+// Row tiles, 3D float64 and pairs leave a sensor step's block maxima as max
+// bits in per-block words (a float's in one half): the block maxima and flags
+// are written from them right after the step, and the words cleared.
+// Pairs: `second` if the second step evaluated the sensor, else the first.
 template <typename C>
-void finish_blocks(lbm_blocks *h) {
-    auto *words = reinterpret_cast<C *>(static_cast<char *>(h->d.buf[LBM_BUF_BLOCK_MAX]) + h->L.acc_off);
-    hipLaunchKernelGGL(finish_blocks_kernel<C>, dim3(grid_for(h->L.nblocks)), dim3(kAuxThreads), 0, h->stream, words,
-                       (int)(8 / sizeof(C)), (int)h->L.nblocks, h->d.sensor_kind == LBM_SENSOR_L2,
+C *sensor_words(lbm_blocks *h, bool second) {
+    auto *acc = reinterpret_cast<C *>(static_cast<char *>(h->d.buf[LBM_BUF_BLOCK_MAX]) + h->L.acc_off);
+    if (!second) return acc;
+    return sizeof(C) == 8 ? reinterpret_cast<C *>(scratch_d(h, h->L.avgmax_off)) : acc + 1;
+}
+
+template <typename C>
+void finish_blocks(lbm_blocks *h, bool pair = false, bool second = false) {
+    hipLaunchKernelGGL(finish_blocks_kernel<C>, dim3(grid_for(h->L.nblocks)), dim3(kAuxThreads), 0, h->stream,
+                       sensor_words<C>(h, second), pair ? sensor_words<C>(h, !second) : nullptr, (int)(8 / sizeof(C)),
+                       (int)h->L.nblocks, h->d.sensor_kind == LBM_SENSOR_L2,
                        static_cast<C *>(h->d.buf[LBM_BUF_BLOCK_MAX]), static_cast<int8_t *>(h->d.buf[LBM_BUF_FLAGS]),
                        h->d.theta_refine, h->d.theta_coarsen);
 }
@@ -488,8 +511,144 @@ void multi_once(lbm_blocks *h, int m) {
     h->step += m;
 }
 
+template <int Q, typename T, typename C, bool SH>
+void launch_pair(lbm_blocks *h, bool s1, bool s2) {
+    LaunchCfg c;
+    c.stream = h->stream;
+    c.tile_x = h->tile_x;
+    c.scheme = h->inplace ? kStream : kPingPong;
+    c.sensor = s1 || s2;
+    c.sensor_kind = h->d.sensor_kind;
+    c.force = h->has_force;
+    c.smag = h->d.smagorinsky > 0.0;
+    void *dst = h->inplace ? h->d.buf[LBM_BUF_F_B] : h->d.buf[h->cur ? LBM_BUF_F_A : LBM_BUF_F_B];
+    PairArgs p = h->pair_args;
+    p.sensor = (s1 ? 1 : 0) | (s2 ? 2 : 0);
+    p.max1 = sensor_words<C>(h, false);
+    p.max2 = sensor_words<C>(h, true);
+    p.max_stride = (int)(8 / sizeof(C));
+    launch_pair_kernel<Q, T, C, SH>(step_args<Q, C>(h, state_ptr(h), dst, h->tile_x), p, c);
+    if (c.sensor) finish_blocks<C>(h, true, s2);
+}
+
+template <int Q>
+void launch_pair_q(lbm_blocks *h, bool s1, bool s2) {
+    switch (h->d.storage) {
+        case LBM_F64: launch_pair<Q, double, double, false>(h, s1, s2); break;
+        case LBM_F32: launch_pair<Q, float, float, false>(h, s1, s2); break;
+        default: launch_pair<Q, float, float, true>(h, s1, s2); break;   // LBM_F32_SHIFTED
+    }
+}
+
+// Two steps in one launch.  In place (entered with F_A in the order after a
+// local step) the state moves to F_B in that order, and the two buffers
+// change roles.
+void pair_once(lbm_blocks *h, int32_t sensor_every) {
+    const int64_t k = h->step + 2;
+    const bool s1 = sensor_every > 0 && (k - 1) % sensor_every == 0;
+    const bool s2 = sensor_every > 0 && k % sensor_every == 0;
+    if (h->d.lattice == 19) launch_pair_q<19>(h, s1, s2);
+    else launch_pair_q<27>(h, s1, s2);
+    if (h->inplace) {
+        std::swap(h->d.buf[LBM_BUF_F_A], h->d.buf[LBM_BUF_F_B]);
+        h->flip ^= 1;
+    } else {
+        h->cur ^= 1;
+    }
+    h->step = k;
+    if (s1 || s2) h->last_sensor_step = s2 ? k : k - 1;
+}
+
+// Whether runs of two steps go to step_pair, and its tiles.
+//
+// A workgroup marches its W x H columns through `chunk` planes.  Measured over
+// W = 24 .. 128 on cubes of 105 to 256 (float32 D3Q19), a plane takes 1.05 us
+// plus 0.62 us per KB of the lines of one population that it reads and writes,
+// as long as the workgroups fit the 256 compute units; so the tile is the one
+// with the least of that, times chunk + 2 planes (two are halo), times the
+// rounds of 256 workgroups.  (Lines written in part do not show on D3Q27,
+// whose planes are longer in arithmetic.)
+//
+// float64 always pairs (96^3 D3Q19: 61.6 us per step one by one, 39.6 in
+// pairs; 24^3 10.4 / 8.4).  Elsewhere a pair is taken when it is the shorter:
+// its planes (longer with Smagorinsky or a force, shorter without the sensor)
+// and 5 us for its start and, with the sensor, the finishing launch, against
+// two steps one by one, which run at 6.8 TB/s plus 4 us while the single buffer of
+// the in-place scheme stays in the 256 MB Infinity Cache and at 5.3 TB/s
+// above.  Per step, one by one / in pairs, sensor at every step: D3Q19 float32
+// 128^3 49.0 / 48.4, 160^3 116 / 90, 192^3 200 / 150, 256^3 439 / 324; a 204 x
+// 100 x 84 grid 42.4 / 44.0 (not paired), without the sensor 42.3 / 38.0;
+// D3Q27 128^3 69 / 85 (not paired), 192^3 286 / 226, 256^3 641 / 542.
+void pair_setting(lbm_blocks *h) {
+    const lbm_desc &d = h->d;
+    const Layout &L = h->L;
+    const bool f64 = d.storage == LBM_F64, smag = d.smagorinsky > 0.0;
+    h->pair_sensor = h->pair_plain = false;
+    const char *env = std::getenv("LBM_PAIR");
+    if (env && std::strcmp(env, "off") == 0) return;
+    if (L.dim != 3 || d.storage > LBM_F32_SHIFTED) return;
+    // as pair_supported
+    if (f64 ? d.lattice != LBM_D3Q19 || h->has_force : h->has_force && smag) return;
+    if (L.bytes[LBM_BUF_F_A] >= (size_t(1) << 32)) return;   // 32-bit byte offsets
+    const int nx = d.extent[0], ny = d.extent[1], nz = d.extent[2];
+    if (nx < 4 || ny < 4 || nz < 4) return;
+    const int cols = d.lattice == LBM_D3Q27 ? pair_columns<27, float>()
+                                            : (f64 ? pair_columns<19, double>() : pair_columns<19, float>());
+    PairArgs p{};
+    double best = 1e300;   // us
+    for (int W = 8; W <= 128; W += 8) {
+        if (W > 8 && W >= nx + 8) break;
+        int H = std::min(cols / (W + 2) - 2, ny);
+        const int nty = (ny + H - 1) / H, ntx = (nx + W - 1) / W;
+        H = (ny + nty - 1) / nty;
+        if ((W / 8 + 1) * (H / 8 + 2) > kPairBlocks) continue;
+        const size_t row = W * L.elem;   // bytes of an own row, and of the lines it touches in part
+        const size_t part = L.q == 19 && (row % 128 || nx * L.elem % 128) ? 128 : 0;
+        const double kb = 1e-3 * L.q / 19.0 * ((H + 2.0) * (double)(row + 2 * L.elem + 128) + H * (double)(row + part));
+        const double plane_us = 1.05 + 0.62 * kb;
+        for (int nzc = 1; nzc <= nz; ++nzc) {
+            const int chunk = (nz + nzc - 1) / nzc;
+            if ((nz + chunk - 1) / chunk != nzc) continue;
+            const int64_t wg = (int64_t)ntx * nty * nzc;
+            const double us = (double)((wg + 255) / 256) * (chunk + 2) * plane_us;
+            if (us < best) {
+                best = us;
+                p.W = W;
+                p.H = H;
+                p.EW = W + 2;
+                p.cols = (W + 2) * (H + 2);
+                p.ntx = ntx;
+                p.nty = nty;
+                p.chunk = chunk;
+                p.ntiles = (int)wg;
+            }
+        }
+    }
+    p.bytes = (uint32_t)L.bytes[LBM_BUF_F_A];
+    for (int f = 0; f < 6; ++f)
+        if (d.face_bc[f] == LBM_BC_WALL && (d.wall_u[f][0] != 0.0 || d.wall_u[f][1] != 0.0 || d.wall_u[f][2] != 0.0))
+            p.moving |= 1u << f;
+    h->pair_args = p;
+    h->pair_sensor = h->pair_plain = true;
+    if (f64 || (env && std::strcmp(env, "on") == 0)) return;   // "on": tests and tuning
+    if (L.q == 27) best *= 1.12;
+    if (smag) best *= L.q == 19 ? 1.2 : 1.3;
+    if (h->has_force) best *= 1.08;
+    const bool cached = h->inplace && L.bytes[LBM_BUF_F_A] <= (size_t(240) << 20);
+    const double one_us = (double)(2 * L.bytes[LBM_BUF_F_A]) / (cached ? 6.8e6 : 5.3e6) + 4.0;
+    h->pair_sensor = best + 5.0 < 2.0 * one_us;
+    h->pair_plain = 0.92 * best + 1.5 < 2.0 * one_us;
+}
+
+// Whether the next two steps are to be one step_pair launch.
+bool pair_ready(const lbm_blocks *h, int32_t sensor_every) {
+    if (h->averaging || (h->inplace && h->phase != 0)) return false;
+    const bool sens = sensor_every > 0 && (h->step + 2) / sensor_every != h->step / sensor_every;
+    return sens ? h->pair_sensor : h->pair_plain;
+}
+
 void drop_graphs(lbm_blocks *h) {
-    for (int p = 0; p < 2; ++p)
+    for (int p = 0; p < 4; ++p)
         if (h->graph[p]) {
             (void)hipGraphExecDestroy(h->graph[p]);
             h->graph[p] = nullptr;
@@ -525,9 +684,15 @@ void multi_run(lbm_blocks *h, int64_t c) {
 lbm_status capture_steps(lbm_blocks *h, int parity) {
     const int64_t s0 = h->step;
     HIP_TRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-    if (h->multi) multi_run(h, h->graph_chunk);
-    else
-        for (int k = 0; k < h->graph_chunk; ++k) step_once(h, 0);
+    if (h->multi) {
+        multi_run(h, h->graph_chunk);
+    } else {
+        // an even number of pairs, so that the state ends in the buffer it started in
+        int k = 0;
+        if (pair_ready(h, 0))
+            for (; k < h->graph_chunk / 4 * 4; k += 2) pair_once(h, 0);
+        for (; k < h->graph_chunk; ++k) step_once(h, 0);
+    }
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamEndCapture(h->stream, &g));
     h->step = s0;   // captured, not run; an even chunk leaves the parity as it was
@@ -612,7 +777,9 @@ lbm_status lbm_create_blocks(const lbm_desc *d, const double *f0_host, lbm_block
     h->wall_mask = 0;
     h->graph_chunk = 0;
     h->multi = (!h->inplace && multi_setting(d, L)) ? kMultiMaxSteps : 0;
-    h->graph[0] = h->graph[1] = nullptr;
+    for (hipGraphExec_t &g : h->graph) g = nullptr;
+    h->flip = 0;
+    pair_setting(h);
     for (int f = 0; f < 6; ++f)
         if (d->face_bc[f] == LBM_BC_WALL) h->wall_mask |= 1u << f;
     h->flags_host.resize(L.nblocks);
@@ -655,7 +822,7 @@ lbm_status lbm_step_n(lbm_blocks *h, int64_t n, int32_t sensor_every) {
         const bool free = c > 0 && n - k >= c && !h->averaging &&
                           (sensor_every == 0 || (h->step + c) / sensor_every == h->step / sensor_every);
         if (free) {
-            const int parity = h->inplace ? h->phase : h->cur;
+            const int parity = 2 * h->flip + (h->inplace ? h->phase : h->cur);
             if (!h->graph[parity]) {
                 st = capture_steps(h, parity);
                 if (st != LBM_OK) return st;
@@ -675,6 +842,11 @@ lbm_status lbm_step_n(lbm_blocks *h, int64_t n, int32_t sensor_every) {
                 k += m;
                 continue;
             }
+        }
+        if (n - k >= 2 && pair_ready(h, sensor_every)) {
+            pair_once(h, sensor_every);
+            k += 2;
+            continue;
         }
         step_once(h, sensor_every);
         ++k;
@@ -779,6 +951,7 @@ lbm_status lbm_sensor_average(lbm_blocks *h, double *block_max_host, int64_t *sa
                        d.extent[2], kBlockEdge, kBlockEdge, bz, h->L.nb[0], h->L.nb[1], h->L.nb[2], inv);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(block_max_host, out, nb * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    clear_second_words(h);   // the maxima lay where a float64 pair folds its second sensor
     HIP_TRY(hipStreamSynchronize(h->stream));
     return LBM_OK;
 }

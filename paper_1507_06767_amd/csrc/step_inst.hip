@@ -12,4 +12,6 @@
 namespace lbm {
 template void launch_step_kernel<LBM_Q, LBM_T, LBM_C, LBM_SH>(const StepArgs<LBM_C> &, const LaunchCfg &);
 template void launch_multi_kernel<LBM_Q, LBM_T, LBM_C, LBM_SH>(const StepArgs<LBM_C> &, int, const LaunchCfg &);
+template void launch_pair_kernel<LBM_Q, LBM_T, LBM_C, LBM_SH>(const StepArgs<LBM_C> &, const PairArgs &,
+                                                              const LaunchCfg &);
 }  // namespace lbm

@@ -1,5 +1,6 @@
 """Step kernel variants at the sizes where they can go wrong: the float64
-block maxima of 3D grids, folded by one atomic maximum per workgroup."""
+block maxima of 3D grids, folded by one atomic maximum per workgroup, and two
+steps per launch (step_pair) against two launches."""
 import numpy as np
 import pytest
 
@@ -57,3 +58,74 @@ def test_float64_block_maxima(lbm, orc, q, n, kind):
     others[-1, -1, -1] = False
     assert (fl[others] == -1).all()
     blk.close()
+
+
+_MOVING = [[0.0, 0.03, 0.01], [0.0, 0.0, 0.0], [0.02, 0.0, 0.01], [0.05, 0.0, -0.02], [0.01, 0.02, 0.0],
+           [0.03, -0.01, 0.0]]
+_PAIR = [
+    # name, n, bc, wall_u, force, smagorinsky, smoothed faces
+    ("cavity", (70, 19, 13), (WALL,) * 6, _lid(0.05), 0.0, 0.0, (0,) * 6),
+    ("channel", (33, 21, 9), (PERIODIC, PERIODIC, WALL, WALL, PERIODIC, PERIODIC), _lid(0.0), 1e-5, 0.0, (0,) * 6),
+    ("box", (20, 17, 18), (PERIODIC,) * 6, _lid(0.0), 0.0, 0.1, (0,) * 6),
+    ("walls_x_z", (24, 16, 17), (WALL, WALL, PERIODIC, PERIODIC, WALL, WALL), _MOVING, 0.0, 0.0, (0,) * 6),
+    ("all_moving", (41, 36, 30), (WALL,) * 6, _MOVING, 0.0, 0.14, (0, 1, 0, 1, 1, 0)),
+    ("narrow", (9, 50, 5), (WALL, WALL, WALL, WALL, PERIODIC, PERIODIC), _MOVING, 1e-5, 0.0, (0,) * 6),
+    ("smallest", (4, 4, 4), (PERIODIC,) * 6, _lid(0.0), 0.0, 0.0, (0,) * 6),
+    ("tiles", (133, 67, 40), (WALL,) * 6, _lid(0.05), 0.0, 0.0, (0, 0, 0, 1, 0, 0)),
+]
+
+
+@pytest.mark.parametrize("chunk", [0, 6], ids=["eager", "graph"])
+@pytest.mark.parametrize("q,storage,streaming", [(19, 0, 1), (19, 1, 1), (19, 1, 2), (19, 2, 1), (19, 2, 2),
+                                                 (27, 1, 1), (27, 2, 2)])
+@pytest.mark.parametrize("case", _PAIR, ids=[c[0] for c in _PAIR])
+def test_pairs_match_single_steps(lbm, monkeypatch, case, q, storage, streaming, chunk):
+    """Two steps per launch give the bits of two launches: populations,
+    fields, block maxima and flags, over odd and even runs, with the sensor
+    at every step and at every third, both sensor kinds, eager and replayed."""
+    import torch
+    name, n, bc, wall_u, force, smag, smooth = case
+    print(f"\n[case] pairs {name} q={q} storage={storage} streaming={streaming} chunk={chunk}", flush=True)
+    runs = []
+    for pair in ("off", "on"):
+        monkeypatch.setenv("LBM_PAIR", pair)
+        got = []
+        for kind, every in ((0, 1), (1, 3)):
+            desc = lbm.make_desc(q, n, bc, 0.65, storage=storage, sensor_kind=kind, wall_u=wall_u,
+                                 force=(force, 0.0, 0.0), smagorinsky=smag, wall_profile=smooth, streaming=streaming)
+            stream = torch.cuda.Stream()
+            blk = lbm.Blocks(desc, stream=stream)
+            if chunk:
+                blk.use_graphs(chunk)
+            blk.set_equilibrium(u=lbm_inputs.velocity_perturbation(n, 0.02, seed=5))
+            for k in (7, 2, 13, 6):
+                blk.step_n(k, every if k != 13 else 0)
+                bm, fl, step, _ = blk.sensor_flags()
+                got += [bm, fl, np.array(step), blk.populations(), *blk.macros()]
+            blk.close()
+        runs.append(got)
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b), f"{name}: pairs differ"
+
+
+def test_float64_average_between_pairs(lbm, monkeypatch):
+    """A float64 pair folds its second sensor where the averaged maxima are
+    returned: runs with averages read in between equal single steps."""
+    n = (24, 16, 17)
+    runs = []
+    for pair in ("off", "on"):
+        monkeypatch.setenv("LBM_PAIR", pair)
+        desc = lbm.make_desc(19, n, (WALL,) * 6, 0.6, storage=lbm.LBM_F64, wall_u=_lid(0.05))
+        blk = lbm.Blocks(desc)
+        blk.step_n(4, 1)
+        blk.average_begin()
+        blk.step_n(5, 1)
+        got = [blk.average()[0]]
+        blk.average_end()
+        for _ in range(3):
+            blk.step_n(4, 2)
+            got += [blk.sensor_flags()[0], blk.average()[0]]
+        blk.close()
+        runs.append(got)
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
