@@ -17,7 +17,9 @@
  *   - Device memory is OWNED BY THE CALLER.  The library never allocates
  *     device memory: the caller sizes the five buffers with
  *     lbm_required_bytes(), allocates them (for instance as torch tensors)
- *     and keeps them alive until lbm_destroy().  The one exception is the
+ *     and keeps them alive until lbm_destroy().  (Host data is read through
+ *     pinned host memory, of which at most two rings of 16 MB and four pieces
+ *     of 256 KB stay idle while there is a handle.)  The one exception is the
  *     32 KiB static workspace of lbm_conservation_noalloc, part of the
  *     library's code object.  Host arrays are only read or written during
  *     the call that receives them.

@@ -635,12 +635,9 @@ lbm_status lbm_hierarchy_sensor(lbm_hierarchy *H, double *block_max_host, int8_t
     if (st != LBM_OK) return st;
     if (H->last_sensor_step < 0) return fail(LBM_ESTATE, "no fine sensor step has run");
     lbm_blocks *h = H->coarse;
-    if (block_max_host)
-        HIP_TRY(hipMemcpyAsync(H->bmax_host.data(), H->buf[LBM_HBUF_BLOCK_MAX], H->bmax_host.size(),
-                               hipMemcpyDeviceToHost, h->stream));
-    if (flags_host)
-        HIP_TRY(hipMemcpyAsync(flags_host, H->buf[LBM_HBUF_FLAGS], H->nblocks, hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(h->reader.read(h->stream, {{block_max_host ? H->bmax_host.data() : nullptr, H->buf[LBM_HBUF_BLOCK_MAX],
+                                        H->bmax_host.size()},
+                                       {flags_host, H->buf[LBM_HBUF_FLAGS], (size_t)H->nblocks}}));
     if (block_max_host) {
         for (int64_t b = 0; b < H->nblocks; ++b) {
             if (h->L.cbytes == 8) block_max_host[b] = reinterpret_cast<const double *>(H->bmax_host.data())[b];
@@ -666,10 +663,9 @@ lbm_status lbm_hierarchy_patch_fields(lbm_hierarchy *H, int32_t patch, double *r
                                          n, rho_d, u_d, f_host ? f_d : nullptr, s);
     });
     HIP_TRY(hipGetLastError());
-    if (rho_host) HIP_TRY(hipMemcpyAsync(rho_host, rho_d, n * 8, hipMemcpyDeviceToHost, s));
-    if (u_host) HIP_TRY(hipMemcpyAsync(u_host, u_d, 3 * n * 8, hipMemcpyDeviceToHost, s));
-    if (f_host) HIP_TRY(hipMemcpyAsync(f_host, f_d, H->q * n * 8, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(H->coarse->reader.read(s, {{rho_host, rho_d, (size_t)n * 8},
+                                       {u_host, u_d, 3 * (size_t)n * 8},
+                                       {f_host, f_d, H->q * (size_t)n * 8}}));
     return LBM_OK;
 }
 

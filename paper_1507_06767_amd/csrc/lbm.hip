@@ -2,8 +2,8 @@
 //
 // Validates descriptors, lays out the caller's buffers, selects the kernel
 // variant for (lattice, storage, sensor, force) and enqueues it on the
-// caller's stream.  The library allocates no device memory; the only host
-// allocation is the handle itself.
+// caller's stream.  The library allocates no device memory; its host
+// allocations are the handle and the pinned memory its reads go through.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -19,6 +19,7 @@
 
 #include "lbm.h"
 #include "aux_kernels.hpp"
+#include "host_read.hpp"
 #include "launch.hpp"
 #include "step_kernel.hpp"
 
@@ -239,6 +240,7 @@ struct lbm_blocks {
     hipGraphExec_t graph[4];  // graph_chunk steps, by buffer parity and flip
     std::vector<int8_t> flags_host;
     std::vector<unsigned char> bmax_host;
+    HostReader reader;        // reads of device memory into the caller's arrays
 };
 
 namespace {
@@ -874,11 +876,8 @@ lbm_status lbm_sensor_flags(lbm_blocks *h, double *block_max_host, int8_t *flags
     if (st != LBM_OK) return st;
     if (h->last_sensor_step < 0) return fail(LBM_ESTATE, "no sensor step has run since the state was set");
     const int64_t nb = h->L.nblocks;
-    HIP_TRY(hipMemcpyAsync(h->bmax_host.data(), h->d.buf[LBM_BUF_BLOCK_MAX], nb * h->L.cbytes,
-                           hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipMemcpyAsync(h->flags_host.data(), h->d.buf[LBM_BUF_FLAGS], nb, hipMemcpyDeviceToHost,
-                           h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(h->reader.read(h->stream, {{h->bmax_host.data(), h->d.buf[LBM_BUF_BLOCK_MAX], nb * h->L.cbytes},
+                                       {h->flags_host.data(), h->d.buf[LBM_BUF_FLAGS], (size_t)nb}}));
     bool nonfinite = false;
     for (int64_t b = 0; b < nb; ++b) {
         const double v = (h->L.cbytes == 8) ? reinterpret_cast<const double *>(h->bmax_host.data())[b]
@@ -912,8 +911,7 @@ lbm_status lbm_sensor_levels(lbm_blocks *h, double a, double b, int32_t lmin, in
     hipLaunchKernelGGL(dilate_kernel, dim3(g), dim3(kAuxThreads), 0, h->stream, lev, lev + nb, h->L.nb[0],
                        h->L.nb[1], h->L.nb[2], buffer);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(levels_host, lev + nb, nb, hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(h->reader.read(h->stream, {{levels_host, lev + nb, (size_t)nb}}));
     return LBM_OK;
 }
 
@@ -950,9 +948,9 @@ lbm_status lbm_sensor_average(lbm_blocks *h, double *block_max_host, int64_t *sa
                        reinterpret_cast<const double *>(scr + h->L.avg_off), out, d.extent[0], d.extent[1],
                        d.extent[2], kBlockEdge, kBlockEdge, bz, h->L.nb[0], h->L.nb[1], h->L.nb[2], inv);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(block_max_host, out, nb * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(h->reader.read(h->stream, {{block_max_host, out, nb * sizeof(double)}}));
     clear_second_words(h);   // the maxima lay where a float64 pair folds its second sensor
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(hipGetLastError());
     return LBM_OK;
 }
 
@@ -975,9 +973,7 @@ lbm_status lbm_get_macros(lbm_blocks *h, double *rho_host, double *u_host) {
                            h->d.force[2]);
     });
     HIP_TRY(hipGetLastError());
-    if (rho_host) HIP_TRY(hipMemcpyAsync(rho_host, rho_d, cells * 8, hipMemcpyDeviceToHost, h->stream));
-    if (u_host) HIP_TRY(hipMemcpyAsync(u_host, u_d, 3 * cells * 8, hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(h->reader.read(h->stream, {{rho_host, rho_d, (size_t)cells * 8}, {u_host, u_d, 3 * (size_t)cells * 8}}));
     return LBM_OK;
 }
 
@@ -1000,8 +996,7 @@ lbm_status lbm_block_means(lbm_blocks *h, double *means_host) {
                        u_d, h->d.extent[0], h->d.extent[1], h->d.extent[2], h->L.nb[0], h->L.nb[1], h->L.nb[2], bz,
                        h->d.rho0, out);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(means_host, out, h->L.nblocks * 4 * 8, hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(h->reader.read(h->stream, {{means_host, out, (size_t)h->L.nblocks * 4 * 8}}));
     return LBM_OK;
 }
 
@@ -1014,12 +1009,14 @@ lbm_status lbm_get_populations(lbm_blocks *h, double *f_host) {
     void *canon = canonical_state(h);
     with_types(h, [&]<int Q, typename T>() {
         Planes<T> p = planes_of<Q, T>(h, canon);
-        for (int i = 0; i < Q && st == LBM_OK; ++i) {
-            hipLaunchKernelGGL((export_plane_kernel<T>), dim3(grid_for(cells)), dim3(kAuxThreads), 0,
-                               h->stream, p.f + (int64_t)i * p.pitch, stage, (int)cells, p.shift[i]);
-            hipError_t e = hipMemcpyAsync(f_host + (int64_t)i * cells, stage, cells * 8,
-                                          hipMemcpyDeviceToHost, h->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+        // four planes at a time: what the staging area holds
+        for (int i = 0; i < Q && st == LBM_OK; i += 4) {
+            const int m = std::min(4, Q - i);
+            for (int k = 0; k < m; ++k)
+                hipLaunchKernelGGL((export_plane_kernel<T>), dim3(grid_for(cells)), dim3(kAuxThreads), 0, h->stream,
+                                   p.f + (int64_t)(i + k) * p.pitch, stage + (int64_t)k * cells, (int)cells,
+                                   p.shift[i + k]);
+            const hipError_t e = h->reader.read(h->stream, {{f_host + (int64_t)i * cells, stage, m * (size_t)cells * 8}});
             if (e != hipSuccess) st = fail(LBM_EHIP, "export: %s", hipGetErrorString(e));
         }
     });
@@ -1116,8 +1113,7 @@ lbm_status lbm_conservation(lbm_blocks *h, double out[4]) {
     });
     hipLaunchKernelGGL(conservation_pass2, dim3(1), dim3(kReduceThreads), 0, h->stream, partial, nwg, res);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(out, res, 4 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(h->reader.read(h->stream, {{out, res, 4 * sizeof(double)}}));
     return LBM_OK;
 }
 
@@ -1180,8 +1176,7 @@ lbm_status lbm_conservation_noalloc(lbm_blocks *h, double out[4]) {
     });
     hipLaunchKernelGGL(conservation_pass2, dim3(1), dim3(kReduceThreads), 0, h->stream, partial, nwg, res);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(out, res, 4 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    HIP_TRY(h->reader.read(h->stream, {{out, res, 4 * sizeof(double)}}, false));
     return LBM_OK;
 }
 

@@ -1,6 +1,7 @@
 """Step kernel variants at the sizes where they can go wrong: the float64
-block maxima of 3D grids, folded by one atomic maximum per workgroup, and two
-steps per launch (step_pair) against two launches."""
+block maxima of 3D grids, folded by one atomic maximum per workgroup, two
+steps per launch (step_pair) against two launches, and host reads around the
+sizes where they change form."""
 import numpy as np
 import pytest
 
@@ -129,3 +130,22 @@ def test_float64_average_between_pairs(lbm, monkeypatch):
         runs.append(got)
     for a, b in zip(*runs):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n", [(3, 5, 1), (64, 128, 1), (64, 129, 1), (257, 511, 1), (1201, 1103, 1)])
+def test_host_reads(lbm, n):
+    """Populations and fields come back whole below, at and above the size of
+    a small read (8192 cells' fields) and of the ring of the large ones."""
+    print(f"\n[case] host reads {n}", flush=True)
+    desc = lbm.make_desc(9, n, (PERIODIC,) * 6, 0.8, storage=lbm.LBM_F64)
+    f = lbm_inputs.random_populations(9, n, seed=n[0])
+    blk = lbm.Blocks(desc, f0=f)
+    for _ in range(2):
+        assert np.array_equal(blk.populations(), f)
+        rho, u = blk.macros()
+        c = np.array([(0, 0), (1, 0), (-1, 0), (0, 1), (0, -1), (1, 1), (-1, -1), (1, -1), (-1, 1)], dtype=float)
+        assert np.allclose(rho, f.sum(0), rtol=1e-14, atol=0)
+        for a in range(2):
+            assert np.allclose(u[a] * rho, np.tensordot(c[:, a], f, axes=1), rtol=0, atol=1e-14)
+        assert not u[2].any()
+    blk.close()
