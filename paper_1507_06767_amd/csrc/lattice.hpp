@@ -48,6 +48,8 @@ struct Lattice<27> {
 
 constexpr int kMaxQ = 27;
 
+constexpr int opposite(int i) { return i == 0 ? 0 : (i & 1) ? i + 1 : i - 1; }
+
 template <int Q, int I>
 struct Vel {
     static constexpr int x = Lattice<Q>::c[I][0];
@@ -55,7 +57,7 @@ struct Vel {
     static constexpr int z = Lattice<Q>::c[I][2];
     static constexpr int len2 = x * x + y * y + z * z;
     static constexpr double w = Lattice<Q>::w_by_len2[len2];
-    static constexpr int opp = (I == 0) ? 0 : ((I & 1) ? I + 1 : I - 1);
+    static constexpr int opp = opposite(I);
 };
 
 // Compile-time loop: f(std::integral_constant<int, I>{}) for I in [B, E).

@@ -443,26 +443,25 @@ void finish_import(lbm_blocks *h) {
     h->phase = 0;
 }
 
-// A buffer holding S_k in natural order: the state buffer for ping-pong; for
-// the in-place scheme, F_B after undoing the slot exchange or the last
-// scatter of F_A.
-void *canonical_state(lbm_blocks *h) {
-    if (!h->inplace) return state_ptr(h);
+// The planes of S_k: the state buffer's; for the in-place scheme those of F_A,
+// read in the exchanged slot order, before a gather step, else those of F_B
+// after undoing the last scatter of F_A.  (128^3 float32: a copy of F_A into
+// natural order took 63 us on each call.)
+template <int Q, typename T>
+Planes<T> canonical_planes(lbm_blocks *h) {
+    if (!h->inplace) return planes_of<Q, T>(h, state_ptr(h));
     void *A = h->d.buf[LBM_BUF_F_A];
     void *B = h->d.buf[LBM_BUF_F_B];
-    with_types(h, [&]<int Q, typename T>() {
-        if (h->phase == 0) {
-            hipLaunchKernelGGL((swap_planes_kernel<Q, T>), dim3(grid_for(h->L.cells)), dim3(kAuxThreads), 0,
-                               h->stream, static_cast<const T *>(A), static_cast<T *>(B), h->L.pitch,
-                               (int)h->L.cells);
-        } else {
-            using C = std::conditional_t<sizeof(T) == 8, double, float>;
-            const StepArgs<C> a = step_args<Q, C>(h, A, B, h->tile_x);
-            hipLaunchKernelGGL((unstream_kernel<Q, T, C>), dim3(grid_for(h->L.cells)), dim3(kAuxThreads), 0,
-                               h->stream, a, static_cast<T *>(B));
-        }
-    });
-    return B;
+    if (h->phase == 0) {
+        Planes<T> p = planes_of<Q, T>(h, A);
+        p.exchanged = true;
+        return p;
+    }
+    using C = std::conditional_t<sizeof(T) == 8, double, float>;
+    const StepArgs<C> a = step_args<Q, C>(h, A, B, h->tile_x);
+    hipLaunchKernelGGL((unstream_kernel<Q, T, C>), dim3(grid_for(h->L.cells)), dim3(kAuxThreads), 0, h->stream, a,
+                       static_cast<T *>(B));
+    return planes_of<Q, T>(h, B);
 }
 
 template <int Q>
@@ -966,10 +965,9 @@ lbm_status lbm_get_macros(lbm_blocks *h, double *rho_host, double *u_host) {
     const int64_t cells = h->L.cells;
     double *rho_d = scratch_d(h, h->L.staging_off);
     double *u_d = rho_d + cells;
-    void *canon = canonical_state(h);
     with_types(h, [&]<int Q, typename T>() {
         hipLaunchKernelGGL((macros_kernel<Q, T>), dim3(grid_for(cells)), dim3(kAuxThreads), 0, h->stream,
-                           planes_of<Q, T>(h, canon), rho_d, u_d, h->d.force[0], h->d.force[1],
+                           canonical_planes<Q, T>(h), rho_d, u_d, h->d.force[0], h->d.force[1],
                            h->d.force[2]);
     });
     HIP_TRY(hipGetLastError());
@@ -981,20 +979,14 @@ lbm_status lbm_block_means(lbm_blocks *h, double *means_host) {
     lbm_status st = check_handle(h);
     if (st != LBM_OK) return st;
     if (!means_host) return fail(LBM_EINVAL, "means_host is NULL");
-    const int64_t cells = h->L.cells;
-    double *rho_d = scratch_d(h, h->L.staging_off);
-    double *u_d = rho_d + cells;
     double *out = scratch_d(h, h->L.means_off);
-    void *canon = canonical_state(h);
-    with_types(h, [&]<int Q, typename T>() {
-        hipLaunchKernelGGL((macros_kernel<Q, T>), dim3(grid_for(cells)), dim3(kAuxThreads), 0, h->stream,
-                           planes_of<Q, T>(h, canon), rho_d, u_d, h->d.force[0], h->d.force[1],
-                           h->d.force[2]);
-    });
     const int bz = h->L.dim == 2 ? 1 : kBlockEdge;
-    hipLaunchKernelGGL(block_means_kernel, dim3(grid_for(h->L.nblocks)), dim3(kAuxThreads), 0, h->stream, rho_d,
-                       u_d, h->d.extent[0], h->d.extent[1], h->d.extent[2], h->L.nb[0], h->L.nb[1], h->L.nb[2], bz,
-                       h->d.rho0, out);
+    const int64_t grid = (int64_t)((h->L.nb[0] + kMeansBlocks - 1) / kMeansBlocks) * h->L.nb[1] * h->L.nb[2];
+    with_types(h, [&]<int Q, typename T>() {
+        hipLaunchKernelGGL((block_means_kernel<Q, T>), dim3((unsigned)grid), dim3(kMeansThreads), kMeansLds, h->stream,
+                           canonical_planes<Q, T>(h), h->d.extent[0], h->d.extent[1], h->d.extent[2], h->L.nb[0], bz,
+                           h->d.rho0, h->d.force[0], h->d.force[1], h->d.force[2], out);
+    });
     HIP_TRY(hipGetLastError());
     HIP_TRY(h->reader.read(h->stream, {{means_host, out, (size_t)h->L.nblocks * 4 * 8}}));
     return LBM_OK;
@@ -1006,15 +998,14 @@ lbm_status lbm_get_populations(lbm_blocks *h, double *f_host) {
     if (!f_host) return fail(LBM_EINVAL, "f_host is NULL");
     const int64_t cells = h->L.cells;
     double *stage = scratch_d(h, h->L.staging_off);
-    void *canon = canonical_state(h);
     with_types(h, [&]<int Q, typename T>() {
-        Planes<T> p = planes_of<Q, T>(h, canon);
+        Planes<T> p = canonical_planes<Q, T>(h);
         // four planes at a time: what the staging area holds
         for (int i = 0; i < Q && st == LBM_OK; i += 4) {
             const int m = std::min(4, Q - i);
             for (int k = 0; k < m; ++k)
                 hipLaunchKernelGGL((export_plane_kernel<T>), dim3(grid_for(cells)), dim3(kAuxThreads), 0, h->stream,
-                                   p.f + (int64_t)(i + k) * p.pitch, stage + (int64_t)k * cells, (int)cells,
+                                   p.f + (int64_t)(p.exchanged ? opposite(i + k) : i + k) * p.pitch, stage + (int64_t)k * cells, (int)cells,
                                    p.shift[i + k]);
             const hipError_t e = h->reader.read(h->stream, {{f_host + (int64_t)i * cells, stage, m * (size_t)cells * 8}});
             if (e != hipSuccess) st = fail(LBM_EHIP, "export: %s", hipGetErrorString(e));
@@ -1106,10 +1097,9 @@ lbm_status lbm_conservation(lbm_blocks *h, double out[4]) {
     double *partial = scratch_d(h, h->L.partial_off);
     double *res = scratch_d(h, h->L.out_off);
     const int nwg = (int)std::min<int64_t>(kMaxPartials, (cells + kReduceThreads - 1) / kReduceThreads);
-    void *canon = canonical_state(h);
     with_types(h, [&]<int Q, typename T>() {
         hipLaunchKernelGGL((conservation_pass1<Q, T>), dim3(nwg), dim3(kReduceThreads), 0, h->stream,
-                           planes_of<Q, T>(h, canon), partial);
+                           canonical_planes<Q, T>(h), partial);
     });
     hipLaunchKernelGGL(conservation_pass2, dim3(1), dim3(kReduceThreads), 0, h->stream, partial, nwg, res);
     HIP_TRY(hipGetLastError());
@@ -1169,10 +1159,9 @@ lbm_status lbm_conservation_noalloc(lbm_blocks *h, double out[4]) {
     // The same kernels, workgroup count and summation order as
     // lbm_conservation, so the totals are the same bits.  Every partial the
     // second pass reads is written by the first, so nothing needs clearing.
-    void *canon = canonical_state(h);
     with_types(h, [&]<int Q, typename T>() {
         hipLaunchKernelGGL((conservation_pass1<Q, T>), dim3(nwg), dim3(kReduceThreads), 0, h->stream,
-                           planes_of<Q, T>(h, canon), partial);
+                           canonical_planes<Q, T>(h), partial);
     });
     hipLaunchKernelGGL(conservation_pass2, dim3(1), dim3(kReduceThreads), 0, h->stream, partial, nwg, res);
     HIP_TRY(hipGetLastError());

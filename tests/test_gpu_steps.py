@@ -149,3 +149,48 @@ def test_host_reads(lbm, n):
             assert np.allclose(u[a] * rho, np.tensordot(c[:, a], f, axes=1), rtol=0, atol=1e-14)
         assert not u[2].any()
     blk.close()
+
+
+@pytest.mark.parametrize("storage", [0, 1, 2, 3], ids=["f64", "f32", "f32s", "f16s"])
+@pytest.mark.parametrize("q,n", [(9, (45, 9, 1)), (19, (8, 8, 8)), (19, (37, 20, 9)), (27, (70, 5, 17))])
+def test_state_reads_in_both_slot_orders(lbm, q, n, storage):
+    """The in-place scheme's state read before a gather step (the exchanged
+    slots, as they lie) and after one (scattered): the populations after k
+    steps are the same read with either scheme, and the fields, block means
+    and totals are those of the populations.  Bounds: float64 sums of q
+    values and, in a block, of up to 512 fields, with one rounding of 2^-53
+    per operation."""
+    print(f"\n[case] state reads q={q} n={n} storage={storage}", flush=True)
+    bc = (PERIODIC,) * 6
+    force = (1e-5, 0.0, 0.0)
+    f0 = 1.0 + 0.02 * np.random.default_rng(5).standard_normal((q, n[2], n[1], n[0]))
+    f0 *= 1.0 / q
+    blks = [lbm.Blocks(lbm.make_desc(q, n, bc, 0.8, storage=storage, force=force, streaming=s), f0=f0)
+            for s in (lbm.LBM_STREAMING_AUTO if q > 9 and storage == 0 else lbm.LBM_STREAMING_INPLACE,   # (3D float64: ping-pong only)
+                      lbm.LBM_STREAMING_PINGPONG)]
+    eps = 2.0 ** -53
+    for k in range(3):
+        f, ref = (b.populations() for b in blks)
+        same = storage < 3 or k == 0   # (16 bits: the two kernels round a product and sum differently)
+        assert not same or (f == ref).all(), k
+        rho, u = blks[0].macros()
+        size = np.abs(f).sum(axis=0)
+        assert (np.abs(rho - f.sum(axis=0)) <= 2 * q * eps * size).all()
+        m = blks[0].block_means()
+        bz = 1 if q == 9 else 8
+        for kb in range(m.shape[0]):
+            for jb in range(m.shape[1]):
+                for ib in range(m.shape[2]):
+                    at = np.s_[bz * kb:bz * kb + bz, 8 * jb:8 * jb + 8, 8 * ib:8 * ib + 8]
+                    want = np.array([(rho[at] - 1.0).mean()] + [u[a][at].mean() for a in range(3)])
+                    bound = 2 * 512 * eps * np.array([np.abs(rho[at] - 1.0).mean()] +
+                                                     [np.abs(u[a][at]).mean() for a in range(3)]) + 4 * eps
+                    assert (np.abs(m[kb, jb, ib] - want) <= bound).all(), (k, kb, jb, ib)
+        total = blks[0].conservation()
+        cells = n[0] * n[1] * n[2]
+        assert abs(total[0] - f.sum()) <= 2 * q * cells * eps * size.sum()
+        assert not same or (np.asarray(total) == np.asarray(blks[1].conservation())).all()
+        for b in blks:
+            b.step_n(1, 0)
+    for b in blks:
+        b.close()
