@@ -25,7 +25,9 @@ committed rocprofv3 counter summary, when it was taken on the current kernel
 source.  The 128^3 in-place state (152 MiB) can stay in the 256 MB Infinity
 Cache (roofline.cache_resident); the default workload therefore also times
 the same step + sensor on the 256^3 cavity in float32 (ping-pong, 2.55 GB
-moved per step, beyond that cache), reported as roofline_cache_proof.  The
+moved per launch, beyond that cache), reported as roofline_cache_proof.  Where
+the library advances two steps per launch ("steps_per_launch": 2, kernel
+"step_pair"), a launch is priced at one read and one write of the state.  The
 CPU baseline is the FP64 oracle timed on the host on a short run of the same
 workload.
 
@@ -105,6 +107,10 @@ def _traffic_from_profile(kernel_tag, source="step_kernel.hpp"):
         return float(vals["hbm_bytes_per_launch"])
     except (KeyError, ValueError):
         return None
+
+
+def _source(kernel):
+    return "pair_kernel.hpp" if kernel == "step_pair" else "step_kernel.hpp"
 
 
 def host_env():
@@ -212,12 +218,21 @@ def flag_agreement(lbm, torch, desc, every, ref, theta, eps=2e-4):
             "oracle": "FP64, same initial state and steps"}
 
 
+def steps_per_launch(lbm, blk, every):
+    """2 where the library advances large 3D states two steps per launch
+    (step_pair), else 1."""
+    st, n = lbm.abi.lbm_get_steps_per_launch(blk.h, every)
+    assert st == lbm.LBM_OK
+    return n
+
+
 def cache_proof_leg(lbm, torch, steps, warmup, every=1):
     """The same step + sensor on the 256^3 cavity, float32, ping-pong: its two
-    1.19 GiB buffers cannot stay in the 256 MB Infinity Cache, so every step
+    1.19 GiB buffers cannot stay in the 256 MB Infinity Cache, so every launch
     streams the state from and to HBM.  Timed like the main leg (HIP events
-    around `steps` back-to-back steps on the library's stream); one kernel
-    runs per step, so the mean step period is its duration."""
+    around `steps` back-to-back steps on the library's stream).  A launch
+    advances one step or, as a pair, two: it reads and writes every population
+    once, so it is priced at one read and one write per launch."""
     import lbm_inputs
     w = lbm_inputs.cavity3d(n=256, storage="f32")
     st, tau = lbm.lbm_tau_from_reynolds(w.lid_speed, w.n_across, w.reynolds)
@@ -236,15 +251,18 @@ def cache_proof_leg(lbm, torch, steps, warmup, every=1):
     ms = a.elapsed_time(b)
     bm, fl, k, nonfinite = blk.sensor_flags()
     sch = blk.scheme()
-    blk.close()
     step_s = ms / 1e3 / steps
+    per_launch = steps_per_launch(lbm, blk, every)
+    blk.close()
     algo = 2 * 19 * 4 * w.cells
-    achieved = algo / step_s / 1e9
-    tag = "cavity256_f32_pingpong"
+    achieved = algo / (per_launch * step_s) / 1e9
+    kernel = "step_pair" if per_launch == 2 else "pingpong"
+    tag = f"cavity256_f32_{kernel}"
     return {"workload": w.name, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-            "traffic": _traffic_from_profile(tag), "kernel": "pingpong",
-            "algorithmic_bytes_per_launch": algo, "per_kernel_us": {"pingpong": round(step_s * 1e6, 2)},
+            "traffic": _traffic_from_profile(tag, _source(kernel)), "kernel": kernel, "steps_per_launch": per_launch,
+            "algorithmic_bytes_per_launch": algo,
+            "per_kernel_us": {kernel: round(per_launch * step_s * 1e6, 2)},
             "mlups": round(w.cells / step_s / 1e6, 1), "steps": steps, "warmup": warmup,
             "sensor_every": every, "scheme": sch, "last_sensor_step": k, "nonfinite": bool(nonfinite),
             "working_set_bytes": algo}
@@ -595,6 +613,9 @@ def main():
         per = {kind: 2 * step_s * t / tot for kind, t in per_raw.items()}
     else:
         per = {kind: step_s for kind in per_raw}
+    per_launch = steps_per_launch(lbm, blk, every)
+    if per_launch == 2:
+        per = {"step_pair": 2 * step_s}
     dominant = max(per, key=per.get)
 
     elem = 8 if storage == lbm.LBM_F64 else (2 if storage >= lbm.LBM_F16_SHIFTED else 4)
@@ -604,7 +625,7 @@ def main():
     per_launch_s = per[dominant]
     achieved = bytes_per_update * w.cells / per_launch_s / 1e9
     tag = f"{args.workload}_{args.storage}_{dominant}"
-    traffic = _traffic_from_profile(tag)
+    traffic = _traffic_from_profile(tag, _source(dominant))
 
     result = {
         "metric": "MLUPS and % HBM roofline for D3Q19 step+sensor; flag agreement vs FP64 oracle",
@@ -627,10 +648,11 @@ def main():
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
                      "kernel": dominant,
+                     "steps_per_launch": per_launch,
                      "algorithmic_bytes_per_launch": bytes_per_update * w.cells,
                      "per_kernel_us": {kd: round(t * 1e6, 2) for kd, t in per.items()},
                      "per_kernel_us_single_launch": {kd: round(t * 1e6, 2) for kd, t in per_raw.items()},
-                     "step_avg_achieved": round(bytes_per_update * w.cells / (sec / args.steps) / 1e9, 1),
+                     "step_avg_achieved": round(bytes_per_update * w.cells / (per_launch * sec / args.steps) / 1e9, 1),
                      "scheme": blk.scheme()},
         "last_sensor_step": k,
         "refine_blocks": int((fl == 1).sum()),

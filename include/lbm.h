@@ -270,6 +270,11 @@ lbm_status lbm_get_scheme(lbm_blocks *h, int32_t *inplace, int32_t *next_is_gath
 lbm_status lbm_set_multistep(lbm_blocks *h, int32_t steps);
 lbm_status lbm_get_multistep(lbm_blocks *h, int32_t *steps);
 
+/* Steps that one launch of a 3D handle advances in lbm_step_n with this
+ * sensor period (the in-place scheme: from a gather step): 2 where pairs of
+ * steps pay for its size, else 1. */
+lbm_status lbm_get_steps_per_launch(lbm_blocks *h, int32_t sensor_every, int32_t *steps);
+
 /* Step counter (number of steps taken since it was last set). */
 lbm_status lbm_get_step(lbm_blocks *h, int64_t *step);
 lbm_status lbm_set_step(lbm_blocks *h, int64_t step);

@@ -98,6 +98,7 @@ def _load_library():
         "lbm_get_step": [H, ctypes.POINTER(ctypes.c_int64)],
         "lbm_set_multistep": [H, ctypes.c_int32],
         "lbm_get_multistep": [H, ctypes.POINTER(ctypes.c_int32)],
+        "lbm_get_steps_per_launch": [H, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)],
         "lbm_get_scheme": [H, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32),
                            ctypes.POINTER(ctypes.c_int32)],
         "lbm_set_step": [H, ctypes.c_int64],
@@ -249,6 +250,12 @@ def lbm_set_multistep(h, steps: int):
 def lbm_get_multistep(h):
     s = ctypes.c_int32(0)
     st = _lib.lbm_get_multistep(h, ctypes.byref(s))
+    return st, s.value
+
+
+def lbm_get_steps_per_launch(h, sensor_every):
+    s = ctypes.c_int32(0)
+    st = _lib.lbm_get_steps_per_launch(h, sensor_every, ctypes.byref(s))
     return st, s.value
 
 

@@ -1075,6 +1075,13 @@ lbm_status lbm_get_multistep(lbm_blocks *h, int32_t *steps) {
     return LBM_OK;
 }
 
+lbm_status lbm_get_steps_per_launch(lbm_blocks *h, int32_t sensor_every, int32_t *steps) {
+    if (!h || !steps) return fail(LBM_EINVAL, "NULL argument");
+    const bool sensor = sensor_every == 1 || sensor_every == 2;   // in every pair
+    *steps = !h->averaging && (sensor ? h->pair_sensor : h->pair_plain) ? 2 : 1;
+    return LBM_OK;
+}
+
 lbm_status lbm_get_step(lbm_blocks *h, int64_t *step) {
     if (!h || !step) return fail(LBM_EINVAL, "NULL argument");
     *step = h->step;
