@@ -643,6 +643,8 @@ void pair_setting(lbm_blocks *h) {
 
 // Whether the next two steps are to be one step_pair launch.
 bool pair_ready(const lbm_blocks *h, int32_t sensor_every) {
+    // (the divisions below cost a 2D grid's host loop 2%: 50 ns of 2.2 us per step)
+    if (!h->pair_plain && !h->pair_sensor) return false;
     if (h->averaging || (h->inplace && h->phase != 0)) return false;
     const bool sens = sensor_every > 0 && (h->step + 2) / sensor_every != h->step / sensor_every;
     return sens ? h->pair_sensor : h->pair_plain;

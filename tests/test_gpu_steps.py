@@ -132,10 +132,10 @@ def test_float64_average_between_pairs(lbm, monkeypatch):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("n", [(3, 5, 1), (64, 128, 1), (64, 129, 1), (257, 511, 1), (1201, 1103, 1)])
+@pytest.mark.parametrize("n", [(3, 5, 1), (64, 129, 1), (128, 128, 1), (128, 129, 1), (257, 511, 1), (1201, 1103, 1)])
 def test_host_reads(lbm, n):
     """Populations and fields come back whole below, at and above the size of
-    a small read (8192 cells' fields) and of the ring of the large ones."""
+    a small read (16384 cells' fields) and of the ring of the large ones."""
     print(f"\n[case] host reads {n}", flush=True)
     desc = lbm.make_desc(9, n, (PERIODIC,) * 6, 0.8, storage=lbm.LBM_F64)
     f = lbm_inputs.random_populations(9, n, seed=n[0])
