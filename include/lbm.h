@@ -159,10 +159,13 @@ typedef struct {
  *                the other as staging when states are read or written, and a
  *                launch of two steps moves the state from one to the other;
  *   BLOCK_MAX  : one float32 (float32/16-bit storages) or float64 (F64) per block,
- *                followed by one 64-bit accumulator word per block;
+ *                followed by one 64-bit accumulator word per block (two in 3D
+ *                float64), which hold the handle's state between calls;
  *   FLAGS      : one int8 per sensor block;
  *   SCRATCH    : staging for host transfers, the conservation partial sums, the
- *                per-cell sums of the time-averaged sensor and the level maps.
+ *                per-cell sums of the time-averaged sensor and the level maps;
+ *                holds nothing between calls but those sums, from
+ *                lbm_sensor_average_begin on.
  * Returns LBM_EINVAL / LBM_ENOTSUP for a bad descriptor. */
 lbm_status lbm_required_bytes(const lbm_desc *d, size_t bytes[LBM_NBUF]);
 

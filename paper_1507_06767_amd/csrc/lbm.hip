@@ -95,7 +95,8 @@ struct Layout {
     int nb[3];
     int64_t nblocks;
     size_t bytes[LBM_NBUF];
-    size_t acc_off;       // per-block accumulator words inside BLOCK_MAX
+    size_t acc_off;       // per-block accumulator words inside BLOCK_MAX ...
+    int64_t acc_words;    // ... and their number: one per block, in 3D float64 two
     size_t staging_off, partial_off, out_off;
     size_t avg_off;       // per-cell running sensor sums in float64 (time average)
     size_t lev_off;       // two per-block int8 level arrays
@@ -173,7 +174,8 @@ lbm_status check_desc(const lbm_desc *d, Layout *L) {
     }
     L->bytes[LBM_BUF_F_A] = L->bytes[LBM_BUF_F_B] = plane * L->q;
     L->acc_off = round_up((size_t)L->nblocks * L->cbytes, kAlign);
-    L->bytes[LBM_BUF_BLOCK_MAX] = L->acc_off + round_up((size_t)L->nblocks * 8, kAlign);
+    L->acc_words = L->nblocks * (dim == 3 && d->storage == LBM_F64 ? 2 : 1);
+    L->bytes[LBM_BUF_BLOCK_MAX] = L->acc_off + round_up((size_t)L->acc_words * 8, kAlign);
     L->bytes[LBM_BUF_FLAGS] = round_up((size_t)L->nblocks, kAlign);
     L->staging_off = 0;
     L->partial_off = round_up((size_t)cells * 8 * 4, kAlign);
@@ -370,35 +372,25 @@ void with_types(lbm_blocks *h, F &&f) {
 
 unsigned grid_for(int64_t n) { return (unsigned)((n + kAuxThreads - 1) / kAuxThreads); }
 
-// Words that a pair's sensors are folded into (zero between steps): float
-// storages use the halves of the blocks' accumulator words, float64 the words
-// for the first step and the averaged sensor's maxima in the scratch buffer
-// for the second, which are cleared here.
-void clear_second_words(lbm_blocks *h) {
-    if (h->L.dim != 3 || h->L.cbytes != 8) return;
-    hipLaunchKernelGGL(zero_words_kernel, dim3(grid_for(h->L.nblocks)), dim3(kAuxThreads), 0, h->stream,
-                       reinterpret_cast<unsigned long long *>(scratch_d(h, h->L.avgmax_off)), (int)h->L.nblocks);
-}
-
 // The step kernel's per-block (count | max) words must read zero before a
 // sensor step; they are cleared whenever a state is installed.
 void reset_accumulators(lbm_blocks *h) {
     auto *acc = reinterpret_cast<unsigned long long *>(static_cast<char *>(h->d.buf[LBM_BUF_BLOCK_MAX]) +
                                                        h->L.acc_off);
-    hipLaunchKernelGGL(zero_words_kernel, dim3(grid_for(h->L.nblocks)), dim3(kAuxThreads), 0, h->stream,
-                       acc, (int)h->L.nblocks);
-    clear_second_words(h);
+    hipLaunchKernelGGL(zero_words_kernel, dim3(grid_for(h->L.acc_words)), dim3(kAuxThreads), 0, h->stream,
+                       acc, (int)h->L.acc_words);
 }
 
 // Row tiles, 3D float64 and pairs leave a sensor step's block maxima as max
 // bits in per-block words (a float's in one half): the block maxima and flags
 // are written from them right after the step, and the words cleared.
-// Pairs: `second` if the second step evaluated the sensor, else the first.
+// Pairs: `second` if the second step evaluated the sensor, else the first; a
+// float's are the halves of one accumulator word, a float64's two words, all
+// of them in BLOCK_MAX, which only this handle's steps write.
 template <typename C>
 C *sensor_words(lbm_blocks *h, bool second) {
     auto *acc = reinterpret_cast<C *>(static_cast<char *>(h->d.buf[LBM_BUF_BLOCK_MAX]) + h->L.acc_off);
-    if (!second) return acc;
-    return sizeof(C) == 8 ? reinterpret_cast<C *>(scratch_d(h, h->L.avgmax_off)) : acc + 1;
+    return second ? acc + (sizeof(C) == 8 ? h->L.nblocks : 1) : acc;
 }
 
 template <typename C>
@@ -950,8 +942,6 @@ lbm_status lbm_sensor_average(lbm_blocks *h, double *block_max_host, int64_t *sa
                        d.extent[2], kBlockEdge, kBlockEdge, bz, h->L.nb[0], h->L.nb[1], h->L.nb[2], inv);
     HIP_TRY(hipGetLastError());
     HIP_TRY(h->reader.read(h->stream, {{block_max_host, out, nb * sizeof(double)}}));
-    clear_second_words(h);   // the maxima lay where a float64 pair folds its second sensor
-    HIP_TRY(hipGetLastError());
     return LBM_OK;
 }
 

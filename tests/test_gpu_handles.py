@@ -1,0 +1,65 @@
+"""What a handle keeps in the caller's buffers between calls: several handles
+with one scratch buffer, and step_n calls recorded in a caller's own graph."""
+import numpy as np
+import pytest
+
+import lbm_inputs
+from lbm_inputs import PERIODIC, WALL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lbm():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_1507_06767_amd as lbm
+    return lbm
+
+
+def _lid(speed):
+    w = [[0.0] * 3 for _ in range(6)]
+    w[3][0] = speed
+    return w
+
+
+@pytest.mark.parametrize("pair", ["off", "on"])
+@pytest.mark.parametrize("q,storage", [(19, 0), (27, 0), (19, 1), (27, 2), (19, 3), (9, 0)])
+def test_shared_scratch(lbm, monkeypatch, q, storage, pair):
+    """SCRATCH holds nothing between calls (the average's sums aside): two
+    handles of different extents with one scratch buffer, which is also
+    written over between the calls, give the bits of handles with their own."""
+    import torch
+    monkeypatch.setenv("LBM_PAIR", pair)
+    print(f"\n[case] shared scratch q={q} storage={storage} pair={pair}", flush=True)
+    flat = q == 9
+    bc = (WALL,) * 4 + ((PERIODIC,) * 2 if flat else (WALL,) * 2)
+    sizes = [(40, 33, 1), (24, 50, 1)] if flat else [(24, 17, 18), (20, 40, 9)]
+
+    def run(shared):
+        blks = []
+        for k, n in enumerate(sizes):
+            blks.append(lbm.Blocks(lbm.make_desc(q, n, bc, 0.65, storage=storage, wall_u=_lid(0.05))))
+        if shared:   # the same handles again, on the larger of the two scratch buffers
+            scratch = max((b._bufs[4] for b in blks), key=lambda t: t.numel())
+            for b in blks:
+                b.close()
+                b.desc.buf[4], b.desc.buf_bytes[4] = scratch.data_ptr(), scratch.numel()
+                st, b.h = lbm.abi.lbm_create_blocks(b.desc, None)
+                assert st == lbm.LBM_OK
+        got = []
+        for b, n in zip(blks, sizes):
+            b.set_equilibrium(u=lbm_inputs.velocity_perturbation(n, 0.02, seed=n[0]))
+        for steps, every in ((2, 1), (4, 1), (3, 2), (4, 2)):
+            for b in blks:
+                b.step_n(steps, every)
+                if shared:
+                    scratch.fill_(0x7f)
+                bm, fl, k, _ = b.sensor_flags()
+                got += [bm, fl, np.array(k), b.block_means(), *b.macros(), b.conservation(), b.populations()]
+        for b in blks:
+            b.close()
+        return got
+
+    for a, b in zip(run(False), run(True)):
+        assert np.array_equal(a, b)
