@@ -156,8 +156,8 @@ typedef struct {
  *   F_A, F_B   : two population arrays of q padded planes each.  Ping-pong
  *                streaming alternates between them; the in-place scheme
  *                (chosen for arrays up to 512 MiB) steps one of them and uses
- *                the other as staging when states are read or written, and a
- *                launch of two steps moves the state from one to the other;
+ *                the other as staging when states are read or written, and
+ *                launches of two steps move the state to it and back;
  *   BLOCK_MAX  : one float32 (float32/16-bit storages) or float64 (F64) per block,
  *                followed by one 64-bit accumulator word per block (two in 3D
  *                float64), which hold the handle's state between calls;
@@ -179,7 +179,10 @@ lbm_status lbm_create_blocks(const lbm_desc *d, const double *f0_host, lbm_block
  * Step k also evaluates the sensor, its block maxima and the flags when
  * sensor_every > 0 and k % sensor_every == 0 (sensor_every == 0: never).
  * Two steps of a 3D float32 or float64 grid may share one launch where that
- * is the faster form; results are identical bit for bit.
+ * is the faster form; results are identical bit for bit.  Such launches come
+ * in twos, so that a call leaves the state of a 3D grid in the buffer where
+ * one launch per step leaves it: a call of an even number of steps, recorded
+ * in a graph of the caller's, advances the state at each replay.
  * Asynchronous: returns once the launches are enqueued. */
 lbm_status lbm_step_n(lbm_blocks *h, int64_t n, int32_t sensor_every);
 
@@ -275,7 +278,7 @@ lbm_status lbm_get_multistep(lbm_blocks *h, int32_t *steps);
 
 /* Steps that one launch of a 3D handle advances in lbm_step_n with this
  * sensor period (the in-place scheme: from a gather step): 2 where pairs of
- * steps pay for its size, else 1. */
+ * steps pay for its size and the call has room for two of them, else 1. */
 lbm_status lbm_get_steps_per_launch(lbm_blocks *h, int32_t sensor_every, int32_t *steps);
 
 /* Step counter (number of steps taken since it was last set). */

@@ -237,7 +237,8 @@ struct lbm_blocks {
     bool pair_sensor, pair_plain;   // two steps are taken by one step_pair launch: with the
                                     // sensor at either of them, without it
     PairArgs pair_args;       // its tiles (the sensor words are filled in per launch)
-    int flip;                 // in place: 1 while the caller's F_A and F_B have changed roles
+    int flip;                 // in place: 1 while the caller's F_A and F_B have changed roles, between the
+                              // two pairs of a step_n call
     int graph_chunk;          // steps per graph replay (even), 0: launch step by step
     hipGraphExec_t graph[4];  // graph_chunk steps, by buffer parity and flip
     std::vector<int8_t> flags_host;
@@ -633,13 +634,48 @@ void pair_setting(lbm_blocks *h) {
     h->pair_plain = 0.92 * best + 1.5 < 2.0 * one_us;
 }
 
-// Whether the next two steps are to be one step_pair launch.
-bool pair_ready(const lbm_blocks *h, int32_t sensor_every) {
+// Whether the two steps after `step` are to be one step_pair launch.
+bool pair_ready(const lbm_blocks *h, int64_t step, int phase, int32_t sensor_every) {
     // (the divisions below cost a 2D grid's host loop 2%: 50 ns of 2.2 us per step)
     if (!h->pair_plain && !h->pair_sensor) return false;
-    if (h->averaging || (h->inplace && h->phase != 0)) return false;
-    const bool sens = sensor_every > 0 && (h->step + 2) / sensor_every != h->step / sensor_every;
+    if (h->averaging || (h->inplace && phase != 0)) return false;
+    const bool sens = sensor_every > 0 && (step + 2) / sensor_every != step / sensor_every;
     return sens ? h->pair_sensor : h->pair_plain;
+}
+
+// The launch that lbm_step_n makes next, `left` steps before its end.
+struct Launch {
+    enum Kind { kOne, kPair, kMulti, kGraph } kind;
+    int64_t steps;
+};
+Launch next_launch(const lbm_blocks *h, int64_t step, int phase, int64_t left, int32_t sensor_every) {
+    const int64_t c = h->graph_chunk;
+    // a graph replay covers steps step+1 .. step+c when none of them is a sensor step
+    if (c > 0 && left >= c && !h->averaging && (sensor_every == 0 || (step + c) / sensor_every == step / sensor_every))
+        return {Launch::kGraph, c};
+    if (h->multi && !h->averaging) {
+        // the sensor-free steps before the next sensor step, in one launch
+        int64_t r = left;
+        if (sensor_every > 0) r = std::min(r, sensor_every - 1 - step % sensor_every);
+        if (r >= 2) return {Launch::kMulti, std::min<int64_t>(r, h->multi)};
+    }
+    if (left >= 2 && pair_ready(h, step, phase, sensor_every)) return {Launch::kPair, 2};
+    return {Launch::kOne, 1};
+}
+
+// Whether another pair follows a pair taken now, `left` steps before the end
+// of an lbm_step_n call.
+bool second_pair_follows(const lbm_blocks *h, int64_t left, int32_t sensor_every) {
+    int64_t step = h->step + 2;
+    int phase = 0;
+    for (left -= 2; left >= 2;) {
+        const Launch l = next_launch(h, step, phase, left, sensor_every);
+        if (l.kind == Launch::kPair) return true;
+        if (l.kind == Launch::kOne) phase ^= 1;
+        step += l.steps;
+        left -= l.steps;
+    }
+    return false;
 }
 
 void drop_graphs(lbm_blocks *h) {
@@ -684,7 +720,7 @@ lbm_status capture_steps(lbm_blocks *h, int parity) {
     } else {
         // an even number of pairs, so that the state ends in the buffer it started in
         int k = 0;
-        if (pair_ready(h, 0))
+        if (pair_ready(h, h->step, h->phase, 0))
             for (; k < h->graph_chunk / 4 * 4; k += 2) pair_once(h, 0);
         for (; k < h->graph_chunk; ++k) step_once(h, 0);
     }
@@ -810,41 +846,32 @@ lbm_status lbm_step_n(lbm_blocks *h, int64_t n, int32_t sensor_every) {
     if (st != LBM_OK) return st;
     if (n < 0) return fail(LBM_EINVAL, "n = %lld < 0", (long long)n);
     if (sensor_every < 0) return fail(LBM_EINVAL, "sensor_every = %d < 0", sensor_every);
-    int64_t k = 0;
-    while (k < n) {
-        const int64_t c = h->graph_chunk;
-        // a graph replay covers steps step+1 .. step+c when none of them is a sensor step
-        const bool free = c > 0 && n - k >= c && !h->averaging &&
-                          (sensor_every == 0 || (h->step + c) / sensor_every == h->step / sensor_every);
-        if (free) {
+    // A pair moves the state to the other buffer once in two steps, so that
+    // pairs are taken in twos: a call then ends in the buffer that it ends in
+    // with one step per launch, for an even number of steps the one that it
+    // started in, and can be recorded and replayed in a caller's graph.
+    bool first_of_two = true;
+    for (int64_t k = 0; k < n;) {
+        Launch l = next_launch(h, h->step, h->phase, n - k, sensor_every);
+        if (l.kind == Launch::kPair && first_of_two && !second_pair_follows(h, n - k, sensor_every))
+            l = {Launch::kOne, 1};
+        k += l.steps;
+        if (l.kind == Launch::kGraph) {
             const int parity = 2 * h->flip + (h->inplace ? h->phase : h->cur);
             if (!h->graph[parity]) {
                 st = capture_steps(h, parity);
                 if (st != LBM_OK) return st;
             }
             HIP_TRY(hipGraphLaunch(h->graph[parity], h->stream));
-            h->step += c;
-            k += c;
-            continue;
-        }
-        if (h->multi && !h->averaging) {
-            // the sensor-free steps before the next sensor step, in one launch
-            int64_t r = n - k;
-            if (sensor_every > 0) r = std::min(r, sensor_every - 1 - h->step % sensor_every);
-            if (r >= 2) {
-                const int m = (int)std::min<int64_t>(r, h->multi);
-                multi_once(h, m);
-                k += m;
-                continue;
-            }
-        }
-        if (n - k >= 2 && pair_ready(h, sensor_every)) {
+            h->step += l.steps;
+        } else if (l.kind == Launch::kMulti) {
+            multi_once(h, (int)l.steps);
+        } else if (l.kind == Launch::kPair) {
             pair_once(h, sensor_every);
-            k += 2;
-            continue;
+            first_of_two = !first_of_two;
+        } else {
+            step_once(h, sensor_every);
         }
-        step_once(h, sensor_every);
-        ++k;
     }
     HIP_TRY(hipGetLastError());
     return LBM_OK;

@@ -63,3 +63,41 @@ def test_shared_scratch(lbm, monkeypatch, q, storage, pair):
 
     for a, b in zip(run(False), run(True)):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("steps", [2, 4, 6, 10])
+@pytest.mark.parametrize("q,storage,streaming", [(19, 0, 1), (19, 1, 1), (19, 1, 2), (19, 2, 2), (27, 2, 2), (19, 3, 2)])
+def test_steps_in_a_callers_graph(lbm, monkeypatch, q, storage, streaming, steps):
+    """An even number of steps, recorded in the caller's graph, advances the
+    state at every replay, also with steps launched in between: the bits of
+    one launch per step."""
+    import torch
+    n = (24, 17, 18)
+    print(f"\n[case] caller's graph q={q} storage={storage} streaming={streaming} steps={steps}", flush=True)
+    runs = []
+    for pair in ("off", "on"):
+        monkeypatch.setenv("LBM_PAIR", pair)
+        for every in (0, 1):
+            stream = torch.cuda.Stream()
+            blk = lbm.Blocks(lbm.make_desc(q, n, (WALL,) * 6, 0.65, storage=storage, wall_u=_lid(0.05),
+                                           streaming=streaming), stream=stream)
+            blk.set_equilibrium(u=lbm_inputs.velocity_perturbation(n, 0.02, seed=5))
+            blk.step_n(2, 1)
+            graph = torch.cuda.CUDAGraph()
+            if pair == "on":
+                with torch.cuda.graph(graph, stream=stream):
+                    blk.step_n(steps, every)
+            for between in (0, 2, 1, 3, 4):
+                blk.step_n(between, every)
+                if between == 1:
+                    blk.step_n(1, every)
+                elif between == 3:
+                    blk.step_n(5, every)
+                with torch.cuda.stream(stream):
+                    graph.replay() if pair == "on" else blk.step_n(steps, every)
+                runs.append((pair, [blk.populations(), blk.sensor_flags()[0]]))
+            blk.close()
+    half = len(runs) // 2
+    for (_, a), (_, b) in zip(runs[:half], runs[half:]):
+        for u, v in zip(a, b):
+            assert np.array_equal(u, v)
