@@ -249,8 +249,11 @@ private:
         } catch (...) {
             return hipErrorOutOfMemory;
         }
-        // a crew that cannot be had in full is a smaller one; the calling thread
-        // copies out itself when there is none
+        // The crew comes when the first piece has: until then the stream may still
+        // be at work on what was enqueued before the read, for any time, and a
+        // crew would spin on it (a read behind 0.29 s of steps kept 9 cores busy
+        // all that time).  A crew that cannot be had in full is a smaller one;
+        // the calling thread copies out itself when there is none.
         const int wanted = workers;
         std::atomic<int> hired{-1};
         auto start = [&](int w) {
@@ -258,13 +261,15 @@ private:
             while ((c = hired.load(std::memory_order_acquire)) < 0) std::this_thread::yield();
             if (w < c) work(w);
         };
-        try {
-            crew.reserve(wanted);
-            for (int w = 0; w < wanted; ++w) crew.emplace_back(start, w);
-        } catch (...) {
-        }
-        workers = (int)crew.size();
-        hired.store(workers, std::memory_order_release);
+        auto hire = [&]() {
+            try {
+                crew.reserve(wanted);
+                for (int w = 0; w < wanted; ++w) crew.emplace_back(start, w);
+            } catch (...) {
+            }
+            workers = (int)crew.size();
+            hired.store(workers, std::memory_order_release);
+        };
 
         hipError_t e = hipSuccess;
         int issued = 0, here = 0;
@@ -278,6 +283,7 @@ private:
             } else if (here < issued) {
                 e = hipEventSynchronize(ring.event[here % kSlots]);
                 if (e != hipSuccess) break;
+                if (here == 0) hire();
                 arrived.store(here + 1, std::memory_order_release);
                 if (workers == 0) {
                     std::memcpy(piece[here].dst, ring.mem + (size_t)(here % kSlots) * kChunk, piece[here].bytes);

@@ -101,3 +101,23 @@ def test_steps_in_a_callers_graph(lbm, monkeypatch, q, storage, streaming, steps
     for (_, a), (_, b) in zip(runs[:half], runs[half:]):
         for u, v in zip(a, b):
             assert np.array_equal(u, v)
+
+
+def test_read_behind_a_long_run_waits_on_one_core(lbm):
+    """A field read while steps are still queued: the wait takes the calling
+    thread's core and at most as much again in the runtime's own threads, not
+    those that copy the data out."""
+    import time
+    import torch
+    blk = lbm.Blocks(lbm.make_desc(19, (256, 256, 256), (WALL,) * 6, 0.65, storage=1, wall_u=_lid(0.05)))
+    rho = np.zeros(blk.cells)                 # 134 MB
+    assert lbm.abi.lbm_get_macros(blk.h, blk.cells, rho, None) == lbm.LBM_OK
+    blk.step_n(1000, 0)                       # about 0.3 s; few enough launches not to wait for room in the queue
+    wall, cpu = time.perf_counter(), time.process_time()
+    assert lbm.abi.lbm_get_macros(blk.h, blk.cells, rho, None) == lbm.LBM_OK
+    wall, cpu = time.perf_counter() - wall, time.process_time() - cpu
+    print(f"\nwaited {wall:.3f} s with {cpu / wall:.2f} cores", flush=True)
+    assert wall > 0.1
+    assert cpu < 2.5 * wall
+    torch.cuda.synchronize()
+    blk.close()
