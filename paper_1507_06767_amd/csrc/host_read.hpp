@@ -6,10 +6,12 @@
 // through its own pinned chunks and copies out of them on the calling thread:
 // 10.7 GB/s into fresh memory (537 MB of a 256^3 grid's fields: 50 ms), where
 // the link moves 57 GB/s.  Here the data comes through pinned memory: small
-// reads through 256 KB, in one go, with one synchronisation for all arrays;
+// reads through 512 KB, in one go, with one synchronisation for all arrays;
 // large ones through a ring of 2 MB chunks, the copies into it
 // overlapping the copies out of it on up to 8 threads (43 to 51 GB/s into
-// fresh memory).  Pinning takes 0.1 ms for the small memory and over a
+// fresh memory).  Between the two the runtime's own way is the faster: the
+// threads take 60 to 100 us to start and the memory is mapped already (kLargeRead).
+// Pinning takes 0.1 ms for the small memory and over a
 // millisecond for a ring, so a read borrows what it needs and gives it back:
 // what is idle (at most two rings and four small pieces) serves the next
 // reads of any handle, and is freed with the last handle.
@@ -78,6 +80,13 @@ struct HostRing {
 // 33 grid, 446 KB, cost 100 us more in 7 pieces through the ring: an event and
 // a wait each.)
 constexpr size_t kSmallRead = size_t(512) << 10;
+// Reads of at least this take the ring.  (us for density and velocity, by the
+// runtime / through the ring: 1 MB 78 / 112, 2 MB 137 / 189, 4 MB 253 / 358,
+// 6 MB 385 / 398, 8 MB 480 / 437, 24 MB 1434 / 770.)  So do all parts of a long
+// array, which is fresh memory where the allocator maps it for itself (32 MB):
+// there the runtime's thread also takes its page faults.
+constexpr size_t kLargeRead = size_t(7) << 20;
+constexpr size_t kLongArray = size_t(32) << 20;
 struct PinnedFree {
     void operator()(char *p) const { (void)hipHostFree(p); }
 };
@@ -156,10 +165,10 @@ public:
     ~HostReader() { HostRingPool::get().leave(); }
 
     // Copies the segments after the work enqueued on `st` and waits for them.
-    // may_allocate false: through the runtime's own staging where no pinned
-    // memory is idle.
+    // may_allocate false: by the runtime's own staging where no pinned memory is
+    // idle.  whole: bytes of the array that the segments are a part of.
     template <int N>
-    hipError_t read(hipStream_t st, const HostSegment (&seg)[N], bool may_allocate = true) {
+    hipError_t read(hipStream_t st, const HostSegment (&seg)[N], bool may_allocate = true, size_t whole = 0) {
         size_t total = 0;
         for (const HostSegment &s : seg)
             if (s.dst) total += (s.bytes + 15) / 16 * 16;
@@ -170,7 +179,7 @@ public:
                 HostRingPool::get().give_back(std::move(mem));
                 return e;
             }
-        } else if (may_allocate && hipGetDevice(&device) == hipSuccess) {
+        } else if ((total >= kLargeRead || whole >= kLongArray) && may_allocate && hipGetDevice(&device) == hipSuccess) {
             if (std::unique_ptr<HostRing> ring = HostRingPool::get().borrow(device)) {
                 const hipError_t e = read_large(st, *ring, seg, N, total);
                 HostRingPool::get().give_back(std::move(ring));

@@ -1026,7 +1026,8 @@ lbm_status lbm_get_populations(lbm_blocks *h, double *f_host) {
                 hipLaunchKernelGGL((export_plane_kernel<T>), dim3(grid_for(cells)), dim3(kAuxThreads), 0, h->stream,
                                    p.f + (int64_t)(p.exchanged ? opposite(i + k) : i + k) * p.pitch, stage + (int64_t)k * cells, (int)cells,
                                    p.shift[i + k]);
-            const hipError_t e = h->reader.read(h->stream, {{f_host + (int64_t)i * cells, stage, m * (size_t)cells * 8}});
+            const hipError_t e = h->reader.read(h->stream, {{f_host + (int64_t)i * cells, stage, m * (size_t)cells * 8}},
+                                                true, Q * (size_t)cells * 8);
             if (e != hipSuccess) st = fail(LBM_EHIP, "export: %s", hipGetErrorString(e));
         }
     });

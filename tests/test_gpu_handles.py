@@ -121,3 +121,53 @@ def test_read_behind_a_long_run_waits_on_one_core(lbm):
     assert cpu < 2.5 * wall
     torch.cuda.synchronize()
     blk.close()
+
+
+@pytest.mark.parametrize("ny", [63, 65, 511, 512, 513, 7167, 7168, 7169])
+def test_reads_around_the_sizes_where_they_change_form(lbm, ny):
+    """Density and velocity of 32 x ny cells, 1 KB a row: small, middle and
+    large reads give the populations' sums."""
+    import torch
+    n = (32, ny, 1)
+    print(f"\n[case] reads of {ny} KB", flush=True)
+    f = lbm_inputs.random_populations(9, n, seed=ny)
+    blk = lbm.Blocks(lbm.make_desc(9, n, (PERIODIC,) * 6, 0.8, storage=0), f0=f)
+    want = f.sum(0).reshape(-1)
+    rho, u = np.full(blk.cells, np.nan), np.full(3 * blk.cells, np.nan)
+    assert lbm.abi.lbm_get_macros(blk.h, blk.cells, rho, u) == lbm.LBM_OK
+    assert np.allclose(rho, want, rtol=1e-14, atol=0) and np.isfinite(u).all()
+    again = np.full(blk.cells, np.nan)
+    assert lbm.abi.lbm_get_macros(blk.h, blk.cells, again, None) == lbm.LBM_OK
+    assert np.array_equal(again, rho)
+    both = blk.macros()
+    assert np.array_equal(both[0].reshape(-1), rho) and np.array_equal(both[1].reshape(-1), u)
+    assert np.array_equal(blk.populations(), f)
+    torch.cuda.synchronize()
+    blk.close()
+
+
+def _least(f, reps=40):
+    import time
+    import torch
+    best = 1e9
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        f()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+def test_middle_reads_take_no_longer_than_plain_copies(lbm):
+    """The fields of a 256^2 grid (2 MB) come in at most 1.35 times what the
+    runtime takes to copy as much into ordinary memory, plus 20 us for the
+    kernel and the second copy."""
+    import torch
+    blk = lbm.Blocks(lbm.make_desc(9, (256, 256, 1), (PERIODIC,) * 6, 0.8, storage=1))
+    rho, u = np.zeros(blk.cells), np.zeros(3 * blk.cells)
+    src, dst = torch.zeros(4 * blk.cells, dtype=torch.float64, device="cuda"), torch.zeros(4 * blk.cells, dtype=torch.float64)
+    plain = _least(lambda: dst.copy_(src))
+    got = _least(lambda: lbm.abi.lbm_get_macros(blk.h, blk.cells, rho, u))
+    print(f"\nplain copy {plain * 1e6:.0f} us, macros {got * 1e6:.0f} us", flush=True)
+    assert got <= 1.35 * plain + 20e-6
+    blk.close()
