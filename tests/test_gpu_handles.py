@@ -171,3 +171,27 @@ def test_middle_reads_take_no_longer_than_plain_copies(lbm):
     print(f"\nplain copy {plain * 1e6:.0f} us, macros {got * 1e6:.0f} us", flush=True)
     assert got <= 1.35 * plain + 20e-6
     blk.close()
+
+
+@pytest.mark.parametrize("ny", [64, 200, 2048, 9000])
+def test_reads_into_pinned_memory(lbm, ny):
+    """Fields into the caller's pinned arrays: the values read into ordinary
+    ones, where only one of the two is pinned too, and for 2 MB at most 0.8
+    times their time (the link moves 57 GB/s, the runtime's staging 18)."""
+    import torch
+    print(f"\n[case] pinned {ny} KB", flush=True)
+    blk = lbm.Blocks(lbm.make_desc(9, (32, ny, 1), (PERIODIC,) * 6, 0.8, storage=0),
+                     f0=lbm_inputs.random_populations(9, (32, ny, 1), seed=ny))
+    rho, u = blk.macros()
+    pin = lambda m: torch.full((m,), float("nan"), dtype=torch.float64).pin_memory().numpy()
+    prho, pu, urho, uu = pin(blk.cells), pin(3 * blk.cells), np.empty(blk.cells), np.empty(3 * blk.cells)
+    for a, b in ((prho, pu), (urho, pu), (prho, uu)):
+        a[:], b[:] = np.nan, np.nan
+        assert lbm.abi.lbm_get_macros(blk.h, blk.cells, a, b) == lbm.LBM_OK
+        assert np.array_equal(a, rho.reshape(-1)) and np.array_equal(b, u.reshape(-1))
+    if ny == 2048:
+        pinned = _least(lambda: lbm.abi.lbm_get_macros(blk.h, blk.cells, prho, pu))
+        plain = _least(lambda: lbm.abi.lbm_get_macros(blk.h, blk.cells, urho, uu))
+        print(f"pinned {pinned * 1e6:.0f} us, ordinary {plain * 1e6:.0f} us", flush=True)
+        assert pinned <= 0.8 * plain
+    blk.close()
