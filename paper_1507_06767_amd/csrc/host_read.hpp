@@ -45,18 +45,35 @@ inline bool known_to_runtime(const void *p) {
     return false;
 }
 
-// Pinned memory, or nullptr.  The allocation does not disturb a stream
-// capture of another thread.
+// While it lives, allocations and frees of this thread do not disturb a stream
+// capture that is under way, here or in another thread.
+class CaptureGuard {
+public:
+    CaptureGuard() : relaxed_(hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess) {}
+    CaptureGuard(const CaptureGuard &) = delete;
+    CaptureGuard &operator=(const CaptureGuard &) = delete;
+    ~CaptureGuard() {
+        if (relaxed_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+    }
+
+private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+    bool relaxed_;
+};
+
+// Pinned memory, or nullptr.
 inline void *pinned_alloc(size_t bytes) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    CaptureGuard guard;
     void *p = nullptr;
     if (hipHostMalloc(&p, bytes, hipHostMallocPortable) != hipSuccess) {
         p = nullptr;
         (void)hipGetLastError();
     }
-    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     return p;
+}
+inline void pinned_free(void *p) {
+    CaptureGuard guard;
+    (void)hipHostFree(p);
 }
 
 // A ring of pinned chunks and an event per chunk, of the device it was made on.
@@ -71,7 +88,7 @@ struct HostRing {
     HostRing(const HostRing &) = delete;
     HostRing &operator=(const HostRing &) = delete;
     ~HostRing() {
-        if (mem) (void)hipHostFree(mem);
+        if (mem) pinned_free(mem);
         for (hipEvent_t e : event)
             if (e) (void)hipEventDestroy(e);
     }
@@ -98,7 +115,7 @@ constexpr size_t kSmallRead = size_t(512) << 10;
 constexpr size_t kLargeRead = size_t(7) << 20;
 constexpr size_t kLongArray = size_t(32) << 20;
 struct PinnedFree {
-    void operator()(char *p) const { (void)hipHostFree(p); }
+    void operator()(char *p) const { pinned_free(p); }
 };
 using SmallPinned = std::unique_ptr<char, PinnedFree>;
 
