@@ -28,14 +28,15 @@ __device__ __forceinline__ double from_store(T v) {
 
 template <typename T>
 struct Planes {
-    T *f;              // plane i at f + i*pitch, or where `exchanged` at f + opp(i)*pitch
+    T *f;              // plane i at f + i*pitch
     int64_t pitch;
     int cells;
-    bool exchanged;    // the slot order of the in-place scheme before a gather step
     double shift[kMaxQ];  // storage shift per population (0 for plain storage)
-    template <int Q, int I>
+    // population I of cell c; EX: plane i at f + opp(i)*pitch, the slot order of
+    // the in-place scheme before a gather step
+    template <int Q, int I, bool EX>
     __device__ __forceinline__ double load(int64_t c) const {
-        return from_store<T>(f[(int64_t)(exchanged ? Vel<Q, I>::opp : I) * pitch + c]);
+        return from_store<T>(f[(int64_t)(EX ? Vel<Q, I>::opp : I) * pitch + c]);
     }
 };
 
@@ -107,14 +108,14 @@ __global__ void equilibrium_kernel(Planes<T> p, const double *rho, const double 
 
 // rho = sum_i S_i and u = (sum_i xi_i S_i - F/2) / rho of a cell, in float64:
 // r = (rho, u).
-template <int Q, typename T>
+template <int Q, bool EX, typename T>
 __device__ __forceinline__ void cell_macros(const Planes<T> &p, int64_t c, double Fx, double Fy, double Fz,
                                             double (&r)[4]) {
     double rho = 0.0, m[3] = {0.0, 0.0, 0.0};
     static_for<0, Q>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         using V = Vel<Q, i>;
-        const double v = p.template load<Q, i>(c);
+        const double v = p.template load<Q, i, EX>(c);
         rho += v + p.shift[i];
         if constexpr (V::x != 0) m[0] += V::x * v;   // the shifts cancel in pairs
         if constexpr (V::y != 0) m[1] += V::y * v;
@@ -126,13 +127,13 @@ __device__ __forceinline__ void cell_macros(const Planes<T> &p, int64_t c, doubl
     r[3] = (m[2] - 0.5 * Fz) / rho;
 }
 
-template <int Q, typename T>
+template <int Q, typename T, bool EX>
 __global__ void macros_kernel(Planes<T> p, double *rho_out, double *u_out, double Fx, double Fy,
                               double Fz) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= p.cells) return;
     double r[4];
-    cell_macros<Q>(p, c, Fx, Fy, Fz, r);
+    cell_macros<Q, EX>(p, c, Fx, Fy, Fz, r);
     if (rho_out) rho_out[c] = r[0];
     if (u_out) {
         u_out[c] = r[1];
@@ -152,7 +153,7 @@ __global__ void macros_kernel(Planes<T> p, double *rho_out, double *u_out, doubl
 // out, 43, and then summed by one thread per block, 182.)
 constexpr int kMeansBlocks = 4, kMeansThreads = 512;
 constexpr int kMeansLds = kMeansBlocks * 512 * 4 * 8;
-template <int Q, typename T>
+template <int Q, typename T, bool EX>
 __global__ __launch_bounds__(kMeansThreads) void block_means_kernel(Planes<T> p, int nx, int ny, int nz, int nbx,
                                                                     int bz, double rho0, double Fx, double Fy,
                                                                     double Fz, double *out) {
@@ -163,7 +164,7 @@ __global__ __launch_bounds__(kMeansThreads) void block_means_kernel(Planes<T> p,
     if (x < nx && y < ny)
         for (int z = z0 + (t >> 8); z < min(nz, z0 + bz); z += kMeansThreads / 256) {
             double r[4];
-            cell_macros<Q>(p, ((int64_t)z * ny + y) * nx + x, Fx, Fy, Fz, r);
+            cell_macros<Q, EX>(p, ((int64_t)z * ny + y) * nx + x, Fx, Fy, Fz, r);
             double *v = vals + ((((tx >> 3) * 8 + z - z0) * 8 + ty) * 8 + ((tx & 7) ^ (tx >> 3))) * 4;
             v[0] = r[0] - rho0;
             v[1] = r[1];
@@ -280,7 +281,9 @@ __device__ __forceinline__ void tree_reduce4(double (*sh)[4], double acc[4]) {
 
 // Pass 1: workgroup g sums cells g*256 + t, stepping by the grid size, into
 // partial[g][4] = (mass, momentum x, y, z).
-template <int Q, typename T>
+// (The slot order is a template parameter: with a select at each load 128^3
+// float64 took 98 us, 20 more.)
+template <int Q, typename T, bool EX>
 __global__ __launch_bounds__(kReduceThreads) void conservation_pass1(Planes<T> p, double *partial) {
     __shared__ double sh[kReduceThreads][4];
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
@@ -289,7 +292,7 @@ __global__ __launch_bounds__(kReduceThreads) void conservation_pass1(Planes<T> p
         static_for<0, Q>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             using V = Vel<Q, i>;
-            const double v = p.template load<Q, i>(c);
+            const double v = p.template load<Q, i, EX>(c);
             acc[0] += v + p.shift[i];
             if constexpr (V::x != 0) acc[1] += V::x * v;
             if constexpr (V::y != 0) acc[2] += V::y * v;

@@ -436,25 +436,35 @@ void finish_import(lbm_blocks *h) {
     h->phase = 0;
 }
 
+// Whether the state's planes lie exchanged: the in-place scheme before a
+// gather step.
+bool exchanged(const lbm_blocks *h) { return h->inplace && h->phase == 0; }
+
 // The planes of S_k: the state buffer's; for the in-place scheme those of F_A,
 // read in the exchanged slot order, before a gather step, else those of F_B
 // after undoing the last scatter of F_A.  (128^3 float32: a copy of F_A into
 // natural order took 63 us on each call.)
 template <int Q, typename T>
 Planes<T> canonical_planes(lbm_blocks *h) {
-    if (!h->inplace) return planes_of<Q, T>(h, state_ptr(h));
+    if (!h->inplace || exchanged(h)) return planes_of<Q, T>(h, state_ptr(h));
     void *A = h->d.buf[LBM_BUF_F_A];
     void *B = h->d.buf[LBM_BUF_F_B];
-    if (h->phase == 0) {
-        Planes<T> p = planes_of<Q, T>(h, A);
-        p.exchanged = true;
-        return p;
-    }
     using C = std::conditional_t<sizeof(T) == 8, double, float>;
     const StepArgs<C> a = step_args<Q, C>(h, A, B, h->tile_x);
     hipLaunchKernelGGL((unstream_kernel<Q, T, C>), dim3(grid_for(h->L.cells)), dim3(kAuxThreads), 0, h->stream, a,
                        static_cast<T *>(B));
     return planes_of<Q, T>(h, B);
+}
+
+// Calls f.template operator()<Q, T, EX>(planes) for the planes of S_k, EX where
+// they lie exchanged.
+template <typename F>
+void with_state(lbm_blocks *h, F &&f) {
+    with_types(h, [&]<int Q, typename T>() {
+        const Planes<T> p = canonical_planes<Q, T>(h);
+        if (exchanged(h)) f.template operator()<Q, T, true>(p);
+        else f.template operator()<Q, T, false>(p);
+    });
 }
 
 template <int Q>
@@ -984,10 +994,9 @@ lbm_status lbm_get_macros(lbm_blocks *h, double *rho_host, double *u_host) {
     const int64_t cells = h->L.cells;
     double *rho_d = scratch_d(h, h->L.staging_off);
     double *u_d = rho_d + cells;
-    with_types(h, [&]<int Q, typename T>() {
-        hipLaunchKernelGGL((macros_kernel<Q, T>), dim3(grid_for(cells)), dim3(kAuxThreads), 0, h->stream,
-                           canonical_planes<Q, T>(h), rho_d, u_d, h->d.force[0], h->d.force[1],
-                           h->d.force[2]);
+    with_state(h, [&]<int Q, typename T, bool EX>(const Planes<T> &p) {
+        hipLaunchKernelGGL((macros_kernel<Q, T, EX>), dim3(grid_for(cells)), dim3(kAuxThreads), 0, h->stream,
+                           p, rho_d, u_d, h->d.force[0], h->d.force[1], h->d.force[2]);
     });
     HIP_TRY(hipGetLastError());
     HIP_TRY(h->reader.read(h->stream, {{rho_host, rho_d, (size_t)cells * 8}, {u_host, u_d, 3 * (size_t)cells * 8}}));
@@ -1001,9 +1010,9 @@ lbm_status lbm_block_means(lbm_blocks *h, double *means_host) {
     double *out = scratch_d(h, h->L.means_off);
     const int bz = h->L.dim == 2 ? 1 : kBlockEdge;
     const int64_t grid = (int64_t)((h->L.nb[0] + kMeansBlocks - 1) / kMeansBlocks) * h->L.nb[1] * h->L.nb[2];
-    with_types(h, [&]<int Q, typename T>() {
-        hipLaunchKernelGGL((block_means_kernel<Q, T>), dim3((unsigned)grid), dim3(kMeansThreads), kMeansLds, h->stream,
-                           canonical_planes<Q, T>(h), h->d.extent[0], h->d.extent[1], h->d.extent[2], h->L.nb[0], bz,
+    with_state(h, [&]<int Q, typename T, bool EX>(const Planes<T> &p) {
+        hipLaunchKernelGGL((block_means_kernel<Q, T, EX>), dim3((unsigned)grid), dim3(kMeansThreads), kMeansLds, h->stream,
+                           p, h->d.extent[0], h->d.extent[1], h->d.extent[2], h->L.nb[0], bz,
                            h->d.rho0, h->d.force[0], h->d.force[1], h->d.force[2], out);
     });
     HIP_TRY(hipGetLastError());
@@ -1017,14 +1026,13 @@ lbm_status lbm_get_populations(lbm_blocks *h, double *f_host) {
     if (!f_host) return fail(LBM_EINVAL, "f_host is NULL");
     const int64_t cells = h->L.cells;
     double *stage = scratch_d(h, h->L.staging_off);
-    with_types(h, [&]<int Q, typename T>() {
-        Planes<T> p = canonical_planes<Q, T>(h);
+    with_state(h, [&]<int Q, typename T, bool EX>(const Planes<T> &p) {
         // four planes at a time: what the staging area holds
         for (int i = 0; i < Q && st == LBM_OK; i += 4) {
             const int m = std::min(4, Q - i);
             for (int k = 0; k < m; ++k)
                 hipLaunchKernelGGL((export_plane_kernel<T>), dim3(grid_for(cells)), dim3(kAuxThreads), 0, h->stream,
-                                   p.f + (int64_t)(p.exchanged ? opposite(i + k) : i + k) * p.pitch, stage + (int64_t)k * cells, (int)cells,
+                                   p.f + (int64_t)(EX ? opposite(i + k) : i + k) * p.pitch, stage + (int64_t)k * cells, (int)cells,
                                    p.shift[i + k]);
             const hipError_t e = h->reader.read(h->stream, {{f_host + (int64_t)i * cells, stage, m * (size_t)cells * 8}},
                                                 true, Q * (size_t)cells * 8);
@@ -1124,9 +1132,8 @@ lbm_status lbm_conservation(lbm_blocks *h, double out[4]) {
     double *partial = scratch_d(h, h->L.partial_off);
     double *res = scratch_d(h, h->L.out_off);
     const int nwg = (int)std::min<int64_t>(kMaxPartials, (cells + kReduceThreads - 1) / kReduceThreads);
-    with_types(h, [&]<int Q, typename T>() {
-        hipLaunchKernelGGL((conservation_pass1<Q, T>), dim3(nwg), dim3(kReduceThreads), 0, h->stream,
-                           canonical_planes<Q, T>(h), partial);
+    with_state(h, [&]<int Q, typename T, bool EX>(const Planes<T> &p) {
+        hipLaunchKernelGGL((conservation_pass1<Q, T, EX>), dim3(nwg), dim3(kReduceThreads), 0, h->stream, p, partial);
     });
     hipLaunchKernelGGL(conservation_pass2, dim3(1), dim3(kReduceThreads), 0, h->stream, partial, nwg, res);
     HIP_TRY(hipGetLastError());
@@ -1186,9 +1193,8 @@ lbm_status lbm_conservation_noalloc(lbm_blocks *h, double out[4]) {
     // The same kernels, workgroup count and summation order as
     // lbm_conservation, so the totals are the same bits.  Every partial the
     // second pass reads is written by the first, so nothing needs clearing.
-    with_types(h, [&]<int Q, typename T>() {
-        hipLaunchKernelGGL((conservation_pass1<Q, T>), dim3(nwg), dim3(kReduceThreads), 0, h->stream,
-                           canonical_planes<Q, T>(h), partial);
+    with_state(h, [&]<int Q, typename T, bool EX>(const Planes<T> &p) {
+        hipLaunchKernelGGL((conservation_pass1<Q, T, EX>), dim3(nwg), dim3(kReduceThreads), 0, h->stream, p, partial);
     });
     hipLaunchKernelGGL(conservation_pass2, dim3(1), dim3(kReduceThreads), 0, h->stream, partial, nwg, res);
     HIP_TRY(hipGetLastError());
