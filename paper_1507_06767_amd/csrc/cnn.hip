@@ -151,6 +151,128 @@ __global__ __launch_bounds__(256) void conv_forward_kernel(const float *x, int n
     store_tile(acc, v0, nv, co0, r, kg, co, co4, bias, relu, mask, y);
 }
 
+// The same convolution for 4 or 16 (padded) input channels with an operand
+// load per tap (the direct form; direct_forward says where it is taken): with CI a compile-time constant, the tap of K step s is s
+// itself (CI = 16) or 4 s + lane group (CI = 4), so its neighbour offset and
+// its bounds test come from the lane's voxel, decomposed once, instead of a
+// division and a 64-bit index per step; a step's source is the lane's base
+// pointer plus the tap's offset.  (The generic kernel spends ~30 VALU per
+// MFMA on that index arithmetic.)  The same operands in the same order as
+// conv_forward_kernel: the same bits.
+// (Workgroup (bx, by) of the launch: voxel tiles 4 bx .. 4 bx + 3, output
+// channels 16 by ..; a body of its own so that a fused launch can run it.)
+
+// WAVES waves per workgroup, one 16-voxel tile each (8 in conv_forward_ci, 4
+// in the data-gradient part of backward_layer_direct).
+template <int CI, int WAVES = 4>
+__device__ __forceinline__ void conv_forward_ci_body(const float *x, int n, int d, int h, int w,
+                                                     const uint16_t *packed, int co, const float *bias, int relu,
+                                                     const float *mask, float *y, int bx, int by) {
+    constexpr int K16 = (kTaps * CI + 15) / 16 * 16, NK = K16 / 16;
+    const int co4 = pad4(co);
+    const int nv = n * d * h * w;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int v0 = (bx * WAVES + wave) * 16;
+    const int co0 = by * 16;
+    // the workgroup's weight operands, the same for all its tiles, staged once
+    // in LDS ([K step][lane], the lane layout of the MFMA operand) before any
+    // wave may leave
+    __shared__ bf16x4 wsh[NK * 64];
+    for (int e = threadIdx.x; e < NK * 64; e += 64 * WAVES) {
+        const int l = e & 63;
+        wsh[e] = *reinterpret_cast<const bf16x4 *>(packed + (int64_t)(co0 + (l & 15)) * K16 + 16 * (e >> 6) +
+                                                   4 * (l >> 4));
+    }
+    __syncthreads();
+    if (v0 >= nv) return;
+    const int r = lane & 15, kg = lane >> 4;
+    const int va = v0 + r;
+    const bool vok = va < nv;
+    const Vox pa = decompose(vok ? va : 0, d, h, w);
+    // is the neighbour at offset -1, 0, +1 along each axis inside the grid
+    const bool zok[3] = {pa.z > 0, true, pa.z < d - 1};
+    const bool yok[3] = {pa.y > 0, true, pa.y < h - 1};
+    const bool xok[3] = {pa.x > 0, true, pa.x < w - 1};
+    const int hw = h * w;
+    const float *xb = x + (int64_t)(vok ? va : 0) * CI + (CI == 16 ? 4 * kg : 0);
+    const bf16x4 *B = wsh + lane;   // B[64 s]: the weight operand of K step s
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if constexpr (CI == 16) {
+        if (w == 16) {
+            // A tile's 16 voxels are one whole grid row (v0 is a multiple of
+            // 16 = w), lane r holding x = r.  The taps 3g, 3g + 1, 3g + 2 of
+            // one (z, y) offset read the same row of the input shifted by x
+            // offsets -1, 0, +1, and a shift of one voxel is a shift of one
+            // lane within each 16-lane row of the operand: load the 9 rows
+            // once and form the other two taps' operands with DPP row shifts
+            // (zero where the shift leaves the row: x = -1 or 16, outside
+            // the grid).  The operands, and so the bits, are those of the
+            // general loop below.  (A row past nv cannot occur: nv is a
+            // multiple of 16.)
+            float4 a[9];
+            bool rok[9];
+#pragma unroll
+            for (int g = 0; g < 9; ++g) {
+                const int dz = g / 3, dy = g % 3;
+                rok[g] = vok && zok[dz] && yok[dy];
+                const int off = ((dz - 1) * hw + (dy - 1) * w) * CI;
+                a[g] = *reinterpret_cast<const float4 *>(xb + (rok[g] ? off : 0));
+            }
+#pragma unroll
+            for (int g = 0; g < 9; ++g) {
+                const bf16x4 zero = {0, 0, 0, 0};
+                const bf16x4 A = rok[g] ? to_bf16x4(a[g].x, a[g].y, a[g].z, a[g].w) : zero;
+                const int2 ai = __builtin_bit_cast(int2, A);
+                // row_shr:1 (lane r takes lane r - 1) and row_shl:1 (lane r + 1), 0 at the row's end
+                const int2 lo = {__builtin_amdgcn_update_dpp(0, ai.x, 0x111, 0xF, 0xF, true),
+                                 __builtin_amdgcn_update_dpp(0, ai.y, 0x111, 0xF, 0xF, true)};
+                const int2 hi = {__builtin_amdgcn_update_dpp(0, ai.x, 0x101, 0xF, 0xF, true),
+                                 __builtin_amdgcn_update_dpp(0, ai.y, 0x101, 0xF, 0xF, true)};
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, lo), B[64 * (3 * g)], acc,
+                                                                0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(A, B[64 * (3 * g + 1)], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, hi), B[64 * (3 * g + 2)],
+                                                                acc, 0, 0, 0);
+            }
+            store_tile(acc, v0, nv, co0, r, kg, co, co4, bias, relu, mask, y);
+            return;
+        }
+    }
+    constexpr int kPass = 9;
+#pragma unroll
+    for (int s0 = 0; s0 < NK; s0 += kPass) {
+        float4 a[kPass];
+        bool ok[kPass];
+#pragma unroll
+        for (int q = 0; q < kPass; ++q) {
+            const int s = s0 + q;
+            if (s < NK) {
+                const int tap = (CI == 16) ? s : 4 * s + kg;   // k = 16 s + 4 kg, tap = k / CI
+                const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;   // offsets + 1
+                ok[q] = vok && tap < kTaps && zok[dz] && yok[dy] && xok[dx];
+                const int off = ((dz - 1) * hw + (dy - 1) * w + (dx - 1)) * CI;
+                a[q] = *reinterpret_cast<const float4 *>(xb + (ok[q] ? off : 0));
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kPass; ++q)
+            if (s0 + q < NK) {
+                // outside the grid: zeros (the load above read the lane's own voxel)
+                const bf16x4 A = to_bf16x4(a[q].x, a[q].y, a[q].z, a[q].w);
+                const bf16x4 zero = {0, 0, 0, 0};
+                acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ok[q] ? A : zero, B[64 * (s0 + q)], acc, 0, 0, 0);
+            }
+    }
+    store_tile(acc, v0, nv, co0, r, kg, co, co4, bias, relu, mask, y);
+}
+
+template <int CI>
+__global__ __launch_bounds__(512) void conv_forward_ci(const float *x, int n, int d, int h, int w,
+                                                       const uint16_t *packed, int co, const float *bias,
+                                                       int relu, const float *mask, float *y) {
+    conv_forward_ci_body<CI, 8>(x, n, d, h, w, packed, co, bias, relu, mask, y, blockIdx.x, blockIdx.y);
+}
+
 // n / by as a multiplication, exact where n by < 2^31: the error of
 // m = floor(2^31 / by) + 1 is at most by / 2^31.
 struct FastDiv {
@@ -443,6 +565,212 @@ __global__ __launch_bounds__(256) void conv_wgrad_kernel(const float *x, const f
     }
 }
 
+// The same weight-gradient partials for 4 or 16 (padded) input channels and
+// rows of a multiple of 4 voxels, of inputs on any alignment, with the operands
+// gathered from memory (the direct form; direct_wgrad says where it is taken):
+// the lane's first voxel is decomposed once
+// and then advanced by 16 voxels per step (carrying into y, z, n), its
+// gradient and input pointers by 16 voxels' strides, so a step is its
+// bounds tests, eight loads and one MFMA.  The same operands in the same
+// order as conv_wgrad_kernel: the same bits.
+// (Workgroup (chunk, bk, bc) of nchunk chunks: a body of its own so that a
+// fused launch can run it.)
+template <int CI>
+__device__ __forceinline__ void conv_wgrad_ci_body(const float *x, const float *gz, int n, int d, int h, int w,
+                                                   int ci, int co, float *work, int chunk, int bk, int bc,
+                                                   int nchunk) {
+    constexpr int K16 = (kTaps * CI + 15) / 16 * 16;
+    const int co4 = pad4(co), co16 = pad16(co);
+    const int nv = n * d * h * w;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k0 = bk * 16, c0 = bc * 16;
+    const int r = lane & 15, kg = lane >> 4;
+    const int kcol = k0 + r;                       // this lane's B column
+    const int tap = kcol / CI, cch = kcol % CI;
+    const bool col_ok = tap < kTaps && cch < ci;
+    const int ocol = c0 + r;                       // this lane's A row (output channel)
+    const bool row_ok = ocol < co;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    float bsum = 0.0f;
+    const int vbeg = chunk * kWgradVoxels + wave * (kWgradVoxels / 4);
+    const int vend = min(vbeg + kWgradVoxels / 4, nv);
+    const int tdz = tap / 9 - 1, tdy = (tap / 3) % 3 - 1, tdx = tap % 3 - 1;
+    const int tdelta = (tdz * h + tdy) * w + tdx;
+    // the lane's 4 voxels of step 0: vq .. vq + 3, one row (w is a multiple of 4)
+    int vq = vbeg + 4 * kg;
+    Vox p = decompose(vq < nv ? vq : 0, d, h, w);
+    const float *gp = gz + (int64_t)vq * co4 + ocol;
+    const float *xp = x + ((int64_t)vq + tdelta) * CI + cch;
+    auto step = [&](const float (&a)[4], const float (&b)[4]) {
+        bsum += ((a[0] + a[1]) + a[2]) + a[3];
+        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(to_bf16x4(a[0], a[1], a[2], a[3]),
+                                                        to_bf16x4(b[0], b[1], b[2], b[3]), acc, 0, 0, 0);
+    };
+    constexpr int kPass = 4;
+    for (int v0 = vbeg; v0 < vend; v0 += 16 * kPass) {
+        float a[kPass][4], b[kPass][4];
+#pragma unroll
+        for (int q = 0; q < kPass; ++q) {
+            const bool zy_ok = col_ok && p.z + tdz >= 0 && p.z + tdz < d && p.y + tdy >= 0 && p.y + tdy < h;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int v = vq + j;
+                const int xx = p.x + j + tdx;
+                const bool oka = v < vend && row_ok;
+                const bool okb = v < vend && zy_ok && xx >= 0 && xx < w;
+                const float av = *(oka ? gp + j * co4 : gz);
+                const float bv = *(okb ? xp + j * CI : x);
+                a[q][j] = oka ? av : 0.0f;
+                b[q][j] = okb ? bv : 0.0f;
+            }
+            // the next 16 voxels
+            vq += 16;
+            gp += 16 * co4;
+            xp += 16 * CI;
+            p.x += 16;
+            while (p.x >= w) {
+                p.x -= w;
+                if (++p.y == h) {
+                    p.y = 0;
+                    if (++p.z == d) p.z = 0;
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kPass; ++q)
+            if (v0 + 16 * q < vend) step(a[q], b[q]);
+    }
+    __shared__ float tile[4][16][16];
+    __shared__ float bias[4][4][16];   // [wave][lane group][channel]
+#pragma unroll
+    for (int j = 0; j < 4; ++j) tile[wave][4 * kg + j][r] = acc[j];
+    bias[wave][kg][r] = bsum;
+    __syncthreads();
+    const int t = threadIdx.x;   // 256 threads = one 16x16 tile
+    const int row = t / 16, col = t % 16;
+    const float sum = ((tile[0][row][col] + tile[1][row][col]) + tile[2][row][col]) + tile[3][row][col];
+    work[((int64_t)chunk * co16 + c0 + row) * K16 + k0 + col] = sum;
+    if (bk == 0 && t < 16) {
+        float bb = 0.0f;
+        for (int wv = 0; wv < 4; ++wv)
+            for (int g = 0; g < 4; ++g) bb += bias[wv][g][t];
+        work[(int64_t)nchunk * co16 * K16 + (int64_t)chunk * co16 + c0 + t] = bb;
+    }
+}
+
+// The weight gradient for 16 (padded) input channels, three taps per
+// workgroup: the taps 3g, 3g + 1, 3g + 2 of one (z, y) offset, whose x
+// offsets are -1, 0, +1 (reduction columns 16 * tap .. + 15).  They share the
+// output-gradient operand, and their input operands are three overlapping
+// windows of one row, so a lane loads the gradient once and the 6 input
+// voxels x - 1 .. x + 4 of its channel once: 10 loads per voxel group
+// instead of 24 with one workgroup per tap (conv_wgrad_ci_body).  Each tap's
+// accumulation takes the same voxels, operands and order as there, so the
+// partials are the same bits; grid (nchunk, 9, co16 / 16).
+__device__ __forceinline__ void conv_wgrad_x3_body(const float *x, const float *gz, int n, int d, int h, int w,
+                                                   int ci, int co, float *work, int chunk, int g, int bc,
+                                                   int nchunk) {
+    constexpr int CI = 16, K16 = kTaps * CI;
+    const int co4 = pad4(co), co16 = pad16(co);
+    const int nv = n * d * h * w;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c0 = bc * 16;
+    const int r = lane & 15, kg = lane >> 4;
+    const bool col_ok = r < ci;                    // this lane's B column: input channel r
+    const int ocol = c0 + r;                       // this lane's A row (output channel)
+    const bool row_ok = ocol < co;
+    const int tdz = g / 3 - 1, tdy = g % 3 - 1;
+    f32x4 acc[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) acc[t] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+    float bsum = 0.0f;
+    const int vbeg = chunk * kWgradVoxels + wave * (kWgradVoxels / 4);
+    const int vend = min(vbeg + kWgradVoxels / 4, nv);
+    // the lane's 4 voxels of step 0: vq .. vq + 3, one row (w is a multiple of 4)
+    int vq = vbeg + 4 * kg;
+    Vox p = decompose(vq < nv ? vq : 0, d, h, w);
+    const float *gp = gz + (int64_t)vq * co4 + ocol;
+    const float *xp = x + ((int64_t)vq + (tdz * h + tdy) * w - 1) * CI + r;   // voxel x - 1 of the row
+    constexpr int kPass = 4;
+    for (int v0 = vbeg; v0 < vend; v0 += 16 * kPass) {
+        float a[kPass][4], b[kPass][6];
+#pragma unroll
+        for (int q = 0; q < kPass; ++q) {
+            // a group of 4 voxels lies wholly before vend or wholly after it
+            const bool vok = vq < vend;
+            const bool zy_ok = vok && col_ok && p.z + tdz >= 0 && p.z + tdz < d && p.y + tdy >= 0 && p.y + tdy < h;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool oka = vok && row_ok;
+                const float av = *(oka ? gp + j * co4 : gz);
+                a[q][j] = oka ? av : 0.0f;
+            }
+#pragma unroll
+            for (int m = 0; m < 6; ++m) {
+                const int xx = p.x + m - 1;
+                const bool okb = zy_ok && xx >= 0 && xx < w;
+                const float bv = *(okb ? xp + m * CI : x);
+                b[q][m] = okb ? bv : 0.0f;
+            }
+            // the next 16 voxels
+            vq += 16;
+            gp += 16 * co4;
+            xp += 16 * CI;
+            p.x += 16;
+            while (p.x >= w) {
+                p.x -= w;
+                if (++p.y == h) {
+                    p.y = 0;
+                    if (++p.z == d) p.z = 0;
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kPass; ++q)
+            if (v0 + 16 * q < vend) {
+                bsum += ((a[q][0] + a[q][1]) + a[q][2]) + a[q][3];
+                const bf16x4 A = to_bf16x4(a[q][0], a[q][1], a[q][2], a[q][3]);
+#pragma unroll
+                for (int t = 0; t < 3; ++t)   // x offset t - 1: voxels j + t - 1 of the window
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                        A, to_bf16x4(b[q][t], b[q][t + 1], b[q][t + 2], b[q][t + 3]), acc[t], 0, 0, 0);
+            }
+    }
+    __shared__ float tile[3][4][16][16];
+    __shared__ float bias[4][4][16];   // [wave][lane group][channel]
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) tile[t][wave][4 * kg + j][r] = acc[t][j];
+    bias[wave][kg][r] = bsum;
+    __syncthreads();
+    const int t = threadIdx.x;   // 256 threads = one 16x16 tile
+    const int row = t / 16, col = t % 16;
+#pragma unroll
+    for (int tt = 0; tt < 3; ++tt) {
+        const float sum = ((tile[tt][0][row][col] + tile[tt][1][row][col]) + tile[tt][2][row][col]) +
+                          tile[tt][3][row][col];
+        work[((int64_t)chunk * co16 + c0 + row) * K16 + (3 * g + tt) * 16 + col] = sum;
+    }
+    if (g == 0 && t < 16) {
+        float bb = 0.0f;
+        for (int wv = 0; wv < 4; ++wv)
+            for (int q = 0; q < 4; ++q) bb += bias[wv][q][t];
+        work[(int64_t)nchunk * co16 * K16 + (int64_t)chunk * co16 + c0 + t] = bb;
+    }
+}
+
+__global__ __launch_bounds__(256) void conv_wgrad_x3(const float *x, const float *gz, int n, int d, int h, int w,
+                                                     int ci, int co, float *work) {
+    conv_wgrad_x3_body(x, gz, n, d, h, w, ci, co, work, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x);
+}
+
+template <int CI>
+__global__ __launch_bounds__(256) void conv_wgrad_ci(const float *x, const float *gz, int n, int d, int h, int w,
+                                                     int ci, int co, float *work) {
+    conv_wgrad_ci_body<CI>(x, gz, n, d, h, w, ci, co, work, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x);
+}
+
 // Rows of the weight gradient's region: chunk `chunk` holds voxels 512 chunk ..,
 // whole and partial rows of the flattened grid; every (n, z) slice it touches
 // gets one more row on either side.
@@ -665,6 +993,27 @@ __global__ __launch_bounds__(kStageThreads, 4) void backward_layer_kernel(const 
     } else {
         const int f = b - nwg;
         conv_forward_body<CIF>(gz, d, h, w, packed_flip, ci, nullptr, 0, mask, gin, g, f % fx, f / fx, lds);
+    }
+}
+
+// The same with the direct forms.
+template <int CIW, int CIF>
+__global__ __launch_bounds__(256) void backward_layer_direct(const float *x, const float *gz, int n, int d, int h,
+                                                             int w, int ci, int co, float *work, int nchunk,
+                                                             int nk, int nc, const uint16_t *packed_flip,
+                                                             const float *mask, float *gin, int fx) {
+    const int nwg = nchunk * nk * nc;
+    const int b = blockIdx.x;
+    if (b < nwg) {
+        if constexpr (CIW == 16)   // nk = 9 groups of three taps
+            conv_wgrad_x3_body(x, gz, n, d, h, w, ci, co, work, b % nchunk, (b / nchunk) % nk, b / (nchunk * nk),
+                               nchunk);
+        else
+            conv_wgrad_ci_body<CIW>(x, gz, n, d, h, w, ci, co, work, b % nchunk, (b / nchunk) % nk,
+                                    b / (nchunk * nk), nchunk);
+    } else {
+        const int f = b - nwg;
+        conv_forward_ci_body<CIF>(gz, n, d, h, w, packed_flip, ci, nullptr, 0, mask, gin, f % fx, f / fx);
     }
 }
 
@@ -994,14 +1343,74 @@ void with_grad(int ci4, int taps, F f) {
 
 bool aligned16(const void *p) { return (uintptr_t)p % 16 == 0; }
 
-// The weight-gradient partials (the staged kernel where it applies).
+// Where the direct forms, an operand load per tap, are the faster ones: in
+// grids of a few ten thousand voxels, whose workgroups all run at once either
+// way, so that staging first only makes each of them longer, and where a
+// staged region is much larger than what it is staged for.  Times in us, direct
+// / staged, replayed from a graph.
+
+// Whether the tiles of a block leave more than a third of its waves' turns idle.
+bool uneven(const Block &g) {
+    const int tiles = (g.nvox + 15) / 16;
+    return 2 * kStageWaves * ((tiles + kStageWaves - 1) / kStageWaves) > 3 * tiles;
+}
+
+// The forward convolution for 4 or 16 padded channels; g: the staged form's
+// blocks, `blocks` of them.  4 channels, whose staging saves least: 8 x 8^3
+// voxels 3.8 / 3.6, 1 x 24^3 3.8 / 4.1, 8 x 16^3 4.1 / 4.4, 3 x 32^3 6.8 / 7.3, 4 x
+// 32^3 8.3 / 7.6, with uneven blocks 16 x 20^3 8.3 / 9.4.  16 channels: rows of 16
+// voxels, where the direct form loads a row once for three taps, 1 x 16^3 4.7 /
+// 5.0, 8 x 16^3 5.0 / 5.5, 24 x 16^3 8.4 / 10.5, 32 x 16^3 11.8 / 10.6; else up to
+// the 256 workgroups of 128 voxels that run at once where the staged form has
+// more: 2 x 24^3 6.5 / 6.9, but 1 x 32^3, of 256, 6.6 / 5.6.
+bool direct_forward(int64_t nv, int wd, int ci4, const Block &g, int64_t blocks) {
+    if (ci4 == 4) return nv < 128 || (nv > 12288 && (nv < (1 << 17) || uneven(g)));
+    if (wd == 16) return nv < 7 * (1 << 14);
+    return nv <= 32768 && blocks > 256 && g.nvox <= 128;
+}
+
+// The weight gradient for 4 or 16 padded input channels and rows of a multiple
+// of 4 voxels, and for 8, whose direct form is the generic kernel; region: the
+// voxels of the staged form's region for 512 of the grid.  4 -> 16 channels: 1 x
+// 4^3 3.9 / 4.7, 1 x 8^3 5.3 / 4.8, 16 x 16 x 200 (region 1616) 6.7 / 7.7, but 8 x
+// 16 x 160 (1458) 5.4 / 5.0, and with all taps in a workgroup 4 x 100 x 240 9.9 /
+// 8.8.  6 -> 16: 1 x 4^3 4.0 / 5.7, 64 x 4^3 (1170) 6.4 / 7.4, 8 x 8^3 (830) 6.3 / 5.8.
+// 16 -> 16: 1 x 4^3 4.3 / 5.8, 1 x 8^3 6.2 / 5.7, 64 x 4^3 6.9 / 7.9, 2 x 16^3 6.0 /
+// 5.9, flat 64 x 48 5.7 / 6.0, 1 x 24^3 6.2 / 7.0, 2 x 24^3 6.8 / 7.1, 8 x 16^3 7.9 /
+// 7.1, 8 x 16 x 160 6.4 / 9.0, 32 x 32 x 160 21.4 / 24.8.
+bool direct_wgrad(int64_t nv, int d, int ci4, int nchunk, int taps, int region) {
+    if (nv < 128) return true;
+    if (ci4 == 4) return taps == 8 && region > 1500;
+    if (nchunk <= 16 && region > 1024) return true;
+    return ci4 == 16 && (region > 1300 || (nchunk <= 16 ? d == 1 : nchunk < 60));
+}
+
+// A layer's backward in one launch, wi and fi the padded input and output
+// channels; g: the staged data gradient's blocks.  16 -> 1: 1 x 8^3 6.2 / 6.6, 1 x
+// 24^3 6.2 / 8.0, 2 x 24^3 7.5 / 8.2, 1 x 32^3 9.0 / 8.4, uneven 8 x 20^3 13.4 / 14.1.
+// 16 -> 16: 2 x 16^3 6.2 / 6.4, flat 64 x 48 5.8 / 6.3, 1 x 24^3 6.3 / 7.5, 6 x 16^3 7.5
+// / 8.7, 2 x 24^3 9.4 / 8.7.  4 -> 16: 2 x 16^3 5.3 / 5.4, 4 x 16^3 5.3 / 5.7, 2 x 20^3
+// 5.7 / 7.8, 2 x 24^3 8.4 / 7.9, 8 x 16^3 6.7 / 7.8, 16 x 16^3 11.3 / 12.0, 8 x 24^3
+// 24.2 / 17.8, 32 x 32 x 160 32.2 / 22.1.
+bool direct_backward(int64_t nv, int d, int wd, int wi, int fi, int nchunk, int taps, int region, const Block &g) {
+    if (nv < 128) return true;
+    if (wi == 4 ? taps == 8 && region > 1500 : region > 1300 || (nchunk <= 16 && region > 1024)) return true;
+    if (wi == 16 && fi == 4) return nv < 32000 || (nv > 40000 && nv < (1 << 18) && uneven(g));
+    if (nv <= 8192) return d == 1;
+    return nv < 27000 || (nv <= 32768 && uneven(g)) || (wi == 4 && wd == 16 && nv <= (1 << 16));
+}
+
+// The weight-gradient partials.
 void launch_wgrad(const float *x, const float *gz, int n, int d, int h, int wd, int ci, int co, float *work,
                   int nchunk, hipStream_t st) {
     const int ci4 = pad4(ci);
     GradRegion g;
     size_t bytes;
     const int taps = grad_taps(ci4, nchunk);
-    if (aligned16(x) && aligned16(gz) && pick_region(d, h, wd, ci4, taps, g, bytes)) {
+    const bool direct = wd % 4 == 0 && (ci4 == 4 || ci4 == 16);
+    const int64_t nv = (int64_t)n * d * h * wd;
+    if (aligned16(x) && aligned16(gz) && pick_region(d, h, wd, ci4, taps, g, bytes) &&
+        !((direct || ci4 == 8) && direct_wgrad(nv, d, ci4, nchunk, taps, g.nr * g.rx))) {
         with_grad(ci4, taps, [&](auto c, auto tp) {
             hipLaunchKernelGGL((conv_wgrad_staged<c(), tp()>), dim3(nchunk, (kTaps + taps - 1) / taps, pad16(co) / 16),
                                dim3(kStageThreads), bytes, st, x, gz, n, d, h, wd, ci, co, work, g);
@@ -1009,7 +1418,13 @@ void launch_wgrad(const float *x, const float *gz, int n, int d, int h, int wd, 
         return;
     }
     const dim3 grid(nchunk, pad16(kTaps * ci4) / 16, pad16(co) / 16);
-    hipLaunchKernelGGL(conv_wgrad_kernel, grid, dim3(256), 0, st, x, gz, n, d, h, wd, ci, co, work);
+    if (!direct)
+        hipLaunchKernelGGL(conv_wgrad_kernel, grid, dim3(256), 0, st, x, gz, n, d, h, wd, ci, co, work);
+    else if (ci4 == 16)
+        hipLaunchKernelGGL(conv_wgrad_x3, dim3(nchunk, kTaps / 3, pad16(co) / 16), dim3(256), 0, st, x, gz, n, d, h,
+                           wd, ci, co, work);
+    else
+        hipLaunchKernelGGL(conv_wgrad_ci<4>, grid, dim3(256), 0, st, x, gz, n, d, h, wd, ci, co, work);
 }
 
 }  // namespace
@@ -1039,9 +1454,10 @@ int32_t lbm_cnn_conv3d_forward(const float *x, int32_t n, int32_t d, int32_t h, 
     const int64_t nv = (int64_t)n * d * h * wd;
     if (nv >= (int64_t(1) << 31)) return -1;
     const int ci4 = pad4(ci);
+    const bool direct = ci4 == 4 || ci4 == 16;
     Block g;
-    if ((ci4 == 4 || ci4 == 8 || ci4 == 16) && pick_block(n, d, h, wd, ci4, 0, g) &&
-        block_count(n, g) < (int64_t(1) << 31)) {
+    if ((direct || ci4 == 8) && pick_block(n, d, h, wd, ci4, 0, g) && block_count(n, g) < (int64_t(1) << 31) &&
+        !(direct && direct_forward(nv, wd, ci4, g, block_count(n, g)))) {
         auto go = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3((unsigned)block_count(n, g), pad16(co) / 16), dim3(kStageThreads),
                                block_lds(g.nreg, ci4), (hipStream_t)stream, x, d, h, wd, packed, co, bias, relu, mask, y, g);
@@ -1051,9 +1467,16 @@ int32_t lbm_cnn_conv3d_forward(const float *x, int32_t n, int32_t d, int32_t h, 
         else go(conv_forward_staged<4>);
         return launched();
     }
-    const dim3 grid(blocks_for(nv, 64), pad16(co) / 16);
-    hipLaunchKernelGGL(conv_forward_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, n, d, h, wd, ci, packed, co,
-                       bias, relu, mask, y);
+    const dim3 grid(blocks_for(nv, direct ? 128 : 64), pad16(co) / 16);
+    if (!direct)
+        hipLaunchKernelGGL(conv_forward_kernel, grid, dim3(256), 0, (hipStream_t)stream, x, n, d, h, wd, ci, packed,
+                           co, bias, relu, mask, y);
+    else if (ci4 == 16)
+        hipLaunchKernelGGL(conv_forward_ci<16>, grid, dim3(512), 0, (hipStream_t)stream, x, n, d, h, wd, packed, co,
+                           bias, relu, mask, y);
+    else
+        hipLaunchKernelGGL(conv_forward_ci<4>, grid, dim3(512), 0, (hipStream_t)stream, x, n, d, h, wd, packed, co,
+                           bias, relu, mask, y);
     return launched();
 }
 
@@ -1102,18 +1525,37 @@ int32_t lbm_cnn_backward_layer(const float *x, const float *gz, int32_t n, int32
     GradRegion gr;
     Block g;
     size_t bytes;
-    if ((wi == 4 || wi == 16) && (fi == 4 || fi == 16) && aligned16(x) && pick_region(d, h, wd, wi, taps, gr, bytes) &&
-        pick_block(n, d, h, wd, fi, (int64_t)nchunk * nk * nc, g)) {
-        const int64_t fx = block_count(n, g), total = (int64_t)nchunk * nk * nc + fx * (pad16(ci) / 16);
-        bytes = std::max(bytes, block_lds(g.nreg, fi));
-        if (total < (int64_t(1) << 31)) {
-            with_grad(wi, taps, [&](auto c, auto tp) {
-                if constexpr (c() != 8) {
-                    auto kern = fi == 16 ? backward_layer_kernel<c(), tp(), 16> : backward_layer_kernel<c(), tp(), 4>;
-                    hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(kStageThreads), bytes, st, x, gz, n, d, h, wd,
-                                       ci, co, work, nchunk, nk, nc, packed_flip, mask, gin, (int)fx, gr, g);
-                }
-            });
+    if ((wi == 4 || wi == 16) && (fi == 4 || fi == 16)) {
+        const bool direct = wd % 4 == 0;
+        if (aligned16(x) && pick_region(d, h, wd, wi, taps, gr, bytes) &&
+            pick_block(n, d, h, wd, fi, (int64_t)nchunk * nk * nc, g) &&
+            !(direct && direct_backward(nv, d, wd, wi, fi, nchunk, taps, gr.nr * gr.rx, g))) {
+            const int64_t fx = block_count(n, g), total = (int64_t)nchunk * nk * nc + fx * (pad16(ci) / 16);
+            bytes = std::max(bytes, block_lds(g.nreg, fi));
+            if (total < (int64_t(1) << 31)) {
+                with_grad(wi, taps, [&](auto c, auto tp) {
+                    if constexpr (c() != 8) {
+                        auto kern = fi == 16 ? backward_layer_kernel<c(), tp(), 16> : backward_layer_kernel<c(), tp(), 4>;
+                        hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(kStageThreads), bytes, st, x, gz, n, d, h,
+                                           wd, ci, co, work, nchunk, nk, nc, packed_flip, mask, gin, (int)fx, gr, g);
+                    }
+                });
+                return launched();
+            }
+        }
+        // weight-gradient workgroups per (chunk, output tile): 16-column tiles, or
+        // for 16 input channels groups of three taps
+        const int nk1 = wi == 16 ? kTaps / 3 : pad16(kTaps * wi) / 16, fx = (int)blocks_for(nv, 64);
+        const int64_t total = (int64_t)nchunk * nk1 * nc + (int64_t)fx * (pad16(ci) / 16);
+        if (direct && total < (int64_t(1) << 31)) {
+            auto go = [&](auto kern) {
+                hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(256), 0, st, x, gz, n, d, h, wd, ci, co, work,
+                                   nchunk, nk1, nc, packed_flip, mask, gin, fx);
+            };
+            if (wi == 16 && fi == 16) go(backward_layer_direct<16, 16>);
+            else if (wi == 16) go(backward_layer_direct<16, 4>);
+            else if (fi == 16) go(backward_layer_direct<4, 16>);
+            else go(backward_layer_direct<4, 4>);
             return launched();
         }
     }
