@@ -41,6 +41,74 @@ def _same(torch, a, b):
     return bool(((a.view(torch.int32) == b.view(torch.int32)) | ((a == 0) & (b == 0))).all())
 
 
+@pytest.mark.parametrize("shape", [(2, 5, 6, 7), (1, 4, 3, 21), (1, 1, 9, 16)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("ci,co", [(20, 16), (32, 32), (32, 1), (128, 5)])
+def test_generic_channels(env, shape, ci, co):
+    """Channel counts that only the generic kernels take: the forward and the
+    masked data gradient (co -> ci channels through ci -> co weights and back)
+    within the float32 accumulation error K u sum |a_k b_k|, u = 2^-23."""
+    torch, cnn = env
+    n, d, h, wd = shape
+    nv = n * d * h * wd
+    print(f"\n[case] generic {shape} {ci}->{co}", flush=True)
+    rng = np.random.default_rng(ci + co + nv)
+    x = rng.standard_normal(shape + (ci,)).astype(np.float32)
+    w = (rng.standard_normal((co, 27, ci)) * 0.2).astype(np.float32)
+    b = (rng.standard_normal(co) * 0.1).astype(np.float32)
+    packed = torch.zeros(cnn.lbm_cnn_packed_size(co, ci), dtype=torch.int16, device="cuda")
+    flip = torch.zeros(cnn.lbm_cnn_packed_size(ci, co), dtype=torch.int16, device="cuda")
+    assert cnn.lbm_cnn_pack_weights(_dev(torch, w), co, ci, 0, packed) == 0
+    assert cnn.lbm_cnn_pack_weights(_dev(torch, w), co, ci, 1, flip) == 0
+    xq, wq = ocnn.bf16_round(x), ocnn.bf16_round(w)
+    ref = ocnn.conv3d(xq, wq, b.astype(np.float64))
+    bound = (27 * ci + 1) * U32 * (ocnn.conv3d(np.abs(xq), np.abs(wq)) + np.abs(b)) + 1e-30
+    y = torch.full((nv, cnn.pad4(co)), float("nan"), dtype=torch.float32, device="cuda")
+    for relu in (0, 1):
+        assert cnn.lbm_cnn_conv3d_forward(_dev(torch, _padded(x, cnn.pad4(ci))), n, d, h, wd, ci, packed, co,
+                                          _dev(torch, b), relu, None, y) == 0
+        got = y.cpu().numpy().astype(np.float64).reshape(shape + (-1,))
+        assert (np.abs(got[..., :co] - (ocnn.relu(ref) if relu else ref)) <= bound).all()
+        assert (got[..., co:] == 0).all()
+
+    # ci channels of gradient: the layer below has co channels, whose weights
+    # are w with the two sides exchanged
+    gz = rng.standard_normal(shape + (co,)).astype(np.float32)
+    act = rng.standard_normal((nv, cnn.pad4(ci))).astype(np.float32)
+    act[::5] = 0.0
+    gin = torch.full((nv, cnn.pad4(ci)), float("nan"), dtype=torch.float32, device="cuda")
+    assert cnn.lbm_cnn_conv3d_forward(_dev(torch, _padded(gz, cnn.pad4(co))), n, d, h, wd, co, flip, ci, None, 0,
+                                      _dev(torch, act), gin) == 0
+    gq = ocnn.bf16_round(gz)
+    ref = ocnn.conv3d_dgrad(gq, wq).reshape(nv, ci) * (act[:, :ci] > 0)
+    bound = 27 * co * U32 * ocnn.conv3d_dgrad(np.abs(gq), np.abs(wq)).reshape(nv, ci) + 1e-30
+    assert (np.abs(gin.cpu().numpy()[:, :ci] - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("channels,shape", [((6, 32, 32, 1), (2, 7, 9, 12)), ((4, 16, 16, 1), (1, 24, 24, 24)),
+                                            ((6, 16, 16, 1), (3, 21, 30, 27))])
+def test_network_gradients(env, channels, shape):
+    """A network with 32-channel layers (generic kernels), and ones of the
+    sizes at which the direct and the staged forms take over: loss and
+    gradients against the oracle with bfloat16-rounded products.  The bound is
+    that of the 16^3 networks: values that round to different sides between
+    layers, 5e-3 in relative L2 norm."""
+    torch, cnn = env
+    from paper_1507_06767_amd.predictor import FlagPredictor
+    print(f"\n[case] network {channels} {shape}", flush=True)
+    net = FlagPredictor(channels=channels, seed=3)
+    rng = np.random.default_rng(9)
+    x = rng.standard_normal(shape + (channels[0],)).astype(np.float32)
+    t = rng.standard_normal(shape).astype(np.float32)
+    loss = net.loss_and_grads(x, t).item()
+    params = [(L.w.cpu().numpy().astype(np.float64), L.b.cpu().numpy().astype(np.float64)) for L in net.layers]
+    ref_loss, ref = ocnn.loss_and_grads(params, x, t, q=ocnn.bf16_round)
+    assert abs(loss - ref_loss) <= 1e-4 * ref_loss
+    for L, (rw, rb) in zip(net.layers, ref):
+        for got, want in ((L.gw, rw), (L.gb, rb)):
+            got = got.cpu().numpy().astype(np.float64)
+            assert np.linalg.norm(got - want) < 5e-3 * np.linalg.norm(want)
+
+
 # voxels on either side of 8,192 and 27,000 (16 channels: taps per workgroup,
 # direct and staged), 65,536 (4 and 8 channels: taps per workgroup) and 131,072;
 # rows of a multiple of 4 voxels (aligned and shifted inputs take the staged or
