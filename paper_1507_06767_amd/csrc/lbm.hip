@@ -571,18 +571,32 @@ void pair_once(lbm_blocks *h, int32_t sensor_every) {
 // as long as the workgroups fit the 256 compute units; so the tile is the one
 // with the least of that, times chunk + 2 planes (two are halo), times the
 // rounds of 256 workgroups.  (Lines written in part do not show on D3Q27,
-// whose planes are longer in arithmetic.)
+// whose planes are longer in arithmetic.)  Tiles of 64 x 8 columns take 1.25
+// times that (2048 x 32 x 32, 64 x 64 x 1000), ones of 64 x 9 do not; the tiles
+// next in line take as long there.
 //
-// float64 always pairs (96^3 D3Q19: 61.6 us per step one by one, 39.6 in
-// pairs; 24^3 10.4 / 8.4).  Elsewhere a pair is taken when it is the shorter:
-// its planes (longer with Smagorinsky or a force, shorter without the sensor)
+// float64 always pairs: of grids from 4^3 to 256^3, flat (1024 x 1024 x 4), long
+// (4 x 4 x 2000, 8 x 8 x 1024, 1000 x 10 x 10) and thin (5 x 400 x 400), none was
+// slower (us per step, one by one / in pairs: 24^3 10.5 / 9.4, 96^3 61.9 / 39.9,
+// 256^3 940 / 599, with Smagorinsky 64^3 22.8 / 22.6).
+//
+// float32 takes a pair where it is the shorter: its planes (longer with
+// Smagorinsky or a force, shorter without the sensor and in shifted storage)
 // and 5 us for its start and, with the sensor, the finishing launch, against
-// two steps one by one, which run at 6.8 TB/s plus 4 us while the single buffer of
-// the in-place scheme stays in the 256 MB Infinity Cache and at 5.3 TB/s
-// above.  Per step, one by one / in pairs, sensor at every step: D3Q19 float32
-// 128^3 49.0 / 48.4, 160^3 116 / 90, 192^3 200 / 150, 256^3 439 / 324; a 204 x
-// 100 x 84 grid 42.4 / 44.0 (not paired), without the sensor 42.3 / 38.0;
-// D3Q27 128^3 69 / 85 (not paired), 192^3 286 / 226, 256^3 641 / 542.
+// two steps one by one.  Those run at 6.8 TB/s plus 4 us (less in short steps)
+// while the single buffer of the in-place scheme stays in the 256 MB Infinity
+// Cache and at 5.3 TB/s above; with the sensor, slices of fewer than 32
+// workgroups add 3 ns per workgroup, as several slices of a block then meet at
+// its word (32 x 32 x 2048 48 us without the sensor, 86 with).  In the cache
+// the estimates are off by 5% and more and a wrong pair costs more than it
+// saves (it also touches both buffers), so that the estimate has to win by 5%
+// there, 3% without the sensor; the KKN sensor and a force weigh more there too,
+// where less time is spent waiting for memory.  Us per step, one by one / in
+// pairs, sensor at every step: D3Q19 float32 128^3 49.6 / 49.0 (not paired), with
+// the KKN sensor 52.5 / 59.1 (not paired), without a sensor 48.5 / 43.8; 160^3 116 / 97, 192^3 200 / 150, 256^3 439 / 324; 204 x 100 x 84
+// 43.1 / 43.6 (not paired), without the sensor 42.4 / 36.5, with a force 43.2 /
+// 45.0 (not paired); 64^3 without the sensor 6.9 / 9.8 (not paired); D3Q27 128^3
+// 70 / 83 (not paired), 192^3 286 / 226, 256^3 641 / 542.
 void pair_setting(lbm_blocks *h) {
     const lbm_desc &d = h->d;
     const Layout &L = h->L;
@@ -635,13 +649,20 @@ void pair_setting(lbm_blocks *h) {
     h->pair_args = p;
     h->pair_sensor = h->pair_plain = true;
     if (f64 || (env && std::strcmp(env, "on") == 0)) return;   // "on": tests and tuning
+    const bool cached = h->inplace && L.bytes[LBM_BUF_F_A] <= (size_t(240) << 20);
+    if (p.W % 64 == 0 && p.H % 8 == 0) best *= 1.25;
+    if (d.storage == LBM_F32_SHIFTED) best *= 0.98;
     if (L.q == 27) best *= 1.12;
     if (smag) best *= L.q == 19 ? 1.2 : 1.3;
-    if (h->has_force) best *= 1.08;
-    const bool cached = h->inplace && L.bytes[LBM_BUF_F_A] <= (size_t(240) << 20);
-    const double one_us = (double)(2 * L.bytes[LBM_BUF_F_A]) / (cached ? 6.8e6 : 5.3e6) + 4.0;
-    h->pair_sensor = best + 5.0 < 2.0 * one_us;
-    h->pair_plain = 0.92 * best + 1.5 < 2.0 * one_us;
+    if (h->has_force) best *= cached ? 1.14 : 1.08;
+    const double with_sensor = best * (cached && d.sensor_kind == LBM_SENSOR_KKN ? 1.2 : 1.0) + 5.0;
+    const double bytes_us = (double)(2 * L.bytes[LBM_BUF_F_A]) / (cached ? 6.8e6 : 5.3e6);
+    double one_sensor = bytes_us + 4.0;
+    const int slice = (nx + h->tile_x - 1) / h->tile_x * ((ny + tile_rows(h->tile_x) - 1) / tile_rows(h->tile_x));
+    if (h->inplace && slice < 32) one_sensor += 0.003 * slice * nz * (1.0 - slice / 32.0);
+    const double one_plain = bytes_us + std::min(4.0, 0.2 * bytes_us);
+    h->pair_sensor = with_sensor < 2.0 * one_sensor * (cached ? 0.95 : 1.0);
+    h->pair_plain = 0.92 * best + 1.5 < 2.0 * one_plain * (cached ? 0.968 : 1.0);
 }
 
 // Whether the two steps after `step` are to be one step_pair launch.
