@@ -1347,7 +1347,9 @@ bool aligned16(const void *p) { return (uintptr_t)p % 16 == 0; }
 // grids of a few ten thousand voxels, whose workgroups all run at once either
 // way, so that staging first only makes each of them longer, and where a
 // staged region is much larger than what it is staged for.  Times in us, direct
-// / staged, replayed from a graph.
+// / staged, in a graph behind a kernel that writes the input anew, as in a
+// network (with inputs left in the caches by the call before, the direct forms
+// gain up to half a microsecond more).
 
 // Whether the tiles of a block leave more than a third of its waves' turns idle.
 bool uneven(const Block &g) {
@@ -1356,28 +1358,28 @@ bool uneven(const Block &g) {
 }
 
 // The forward convolution for 4 or 16 padded channels; g: the staged form's
-// blocks, `blocks` of them.  4 channels, whose staging saves least: 8 x 8^3
-// voxels 3.8 / 3.6, 1 x 24^3 3.8 / 4.1, 8 x 16^3 4.1 / 4.4, 3 x 32^3 6.8 / 7.3, 4 x
-// 32^3 8.3 / 7.6, with uneven blocks 16 x 20^3 8.3 / 9.4.  16 channels: rows of 16
-// voxels, where the direct form loads a row once for three taps, 1 x 16^3 4.7 /
-// 5.0, 8 x 16^3 5.0 / 5.5, 24 x 16^3 8.4 / 10.5, 32 x 16^3 11.8 / 10.6; else up to
-// the 256 workgroups of 128 voxels that run at once where the staged form has
-// more: 2 x 24^3 6.5 / 6.9, but 1 x 32^3, of 256, 6.6 / 5.6.
+// blocks, `blocks` of them.  4 channels, whose staging saves least: 1 x 4^3 2.8 /
+// 3.4, 2 x 16^3 3.9 / 3.8, 1 x 24^3 3.7 / 4.2, 8 x 16^3 4.4 / 4.6, 4 x 24^3 6.0 / 6.4,
+// 1 x 48^3 9.4 / 8.6, 4 x 32^3 8.4 / 7.7, with uneven blocks 16 x 20^3 9.9 / 10.8.  16
+// channels: rows of 16 voxels, where the direct form loads a row once for three
+// taps, 1 x 16^3 4.7 / 4.9, 6 x 16^3 6.1 / 6.2, 8 x 16^3 6.8 / 6.7, 32 x 16^3 18.1 /
+// 13.4; else up to the 256 workgroups of 128 voxels that run at once where the
+// staged form has more: 2 x 24^3 7.8 / 8.5, but 1 x 32^3, of 256, 7.1 / 6.4.
 bool direct_forward(int64_t nv, int wd, int ci4, const Block &g, int64_t blocks) {
-    if (ci4 == 4) return nv < 128 || (nv > 12288 && (nv < (1 << 17) || uneven(g)));
-    if (wd == 16) return nv < 7 * (1 << 14);
+    if (ci4 == 4) return nv < 128 || (nv > 12288 && (nv < 100000 || uneven(g)));
+    if (wd == 16) return nv < 28000;
     return nv <= 32768 && blocks > 256 && g.nvox <= 128;
 }
 
 // The weight gradient for 4 or 16 padded input channels and rows of a multiple
 // of 4 voxels, and for 8, whose direct form is the generic kernel; region: the
 // voxels of the staged form's region for 512 of the grid.  4 -> 16 channels: 1 x
-// 4^3 3.9 / 4.7, 1 x 8^3 5.3 / 4.8, 16 x 16 x 200 (region 1616) 6.7 / 7.7, but 8 x
-// 16 x 160 (1458) 5.4 / 5.0, and with all taps in a workgroup 4 x 100 x 240 9.9 /
-// 8.8.  6 -> 16: 1 x 4^3 4.0 / 5.7, 64 x 4^3 (1170) 6.4 / 7.4, 8 x 8^3 (830) 6.3 / 5.8.
-// 16 -> 16: 1 x 4^3 4.3 / 5.8, 1 x 8^3 6.2 / 5.7, 64 x 4^3 6.9 / 7.9, 2 x 16^3 6.0 /
-// 5.9, flat 64 x 48 5.7 / 6.0, 1 x 24^3 6.2 / 7.0, 2 x 24^3 6.8 / 7.1, 8 x 16^3 7.9 /
-// 7.1, 8 x 16 x 160 6.4 / 9.0, 32 x 32 x 160 21.4 / 24.8.
+// 4^3 3.8 / 4.7, 1 x 8^3 5.2 / 4.7, 16 x 16 x 200 (region 1616) 8.7 / 9.8, but 8 x
+// 16 x 160 (1458) 5.7 / 5.2, and with all taps in a workgroup 4 x 100 x 240 14.0 /
+// 10.3.  6 -> 16: 1 x 4^3 4.0 / 5.7, 64 x 4^3 (1170) 6.4 / 7.4, 8 x 8^3 (830) 6.3 / 5.8.
+// 16 -> 16: 1 x 4^3 4.2 / 5.7, 1 x 8^3 6.1 / 5.8, 64 x 4^3 6.7 / 7.9, 2 x 16^3 5.9 /
+// 5.9, flat 64 x 48 5.6 / 5.9, 1 x 24^3 6.8 / 7.5, 2 x 24^3 8.1 / 8.4, 8 x 16^3 8.6 /
+// 7.8, 8 x 16 x 160 6.6 / 9.3, 32 x 32 x 160 24.9 / 28.2.
 bool direct_wgrad(int64_t nv, int d, int ci4, int nchunk, int taps, int region) {
     if (nv < 128) return true;
     if (ci4 == 4) return taps == 8 && region > 1500;
@@ -1386,18 +1388,20 @@ bool direct_wgrad(int64_t nv, int d, int ci4, int nchunk, int taps, int region) 
 }
 
 // A layer's backward in one launch, wi and fi the padded input and output
-// channels; g: the staged data gradient's blocks.  16 -> 1: 1 x 8^3 6.2 / 6.6, 1 x
-// 24^3 6.2 / 8.0, 2 x 24^3 7.5 / 8.2, 1 x 32^3 9.0 / 8.4, uneven 8 x 20^3 13.4 / 14.1.
-// 16 -> 16: 2 x 16^3 6.2 / 6.4, flat 64 x 48 5.8 / 6.3, 1 x 24^3 6.3 / 7.5, 6 x 16^3 7.5
-// / 8.7, 2 x 24^3 9.4 / 8.7.  4 -> 16: 2 x 16^3 5.3 / 5.4, 4 x 16^3 5.3 / 5.7, 2 x 20^3
-// 5.7 / 7.8, 2 x 24^3 8.4 / 7.9, 8 x 16^3 6.7 / 7.8, 16 x 16^3 11.3 / 12.0, 8 x 24^3
-// 24.2 / 17.8, 32 x 32 x 160 32.2 / 22.1.
+// channels; g: the staged data gradient's blocks.  16 -> 1: 1 x 8^3 6.1 / 6.6, 1 x
+// 24^3 6.3 / 8.0, 2 x 24^3 7.9 / 8.7, 1 x 32^3 9.2 / 8.6, uneven 16 x 20^3 25.4 / 26.9.
+// 16 -> 16: 2 x 16^3 6.3 / 6.5, flat 64 x 48 5.7 / 6.2, 1 x 24^3 7.5 / 8.1, 2 x 20^3 8.1
+// / 9.1, 6 x 16^3 8.5 / 9.6, 2 x 24^3 11.2 / 10.2, uneven 4 x 20^3 12.9 / 13.6.  4 ->
+// 16: 2 x 16^3 5.2 / 5.6, 1 x 24^3 7.3 / 6.5, uneven 2 x 20^3 7.3 / 8.6, 6 x 16^3 7.4 /
+// 8.9, 8 x 16^3 8.5 / 9.2, 16 x 16^3 14.2 / 14.8, 8 x 24^3 28.9 / 22.6, 32 x 32 x 160
+// 38.6 / 27.7.
 bool direct_backward(int64_t nv, int d, int wd, int wi, int fi, int nchunk, int taps, int region, const Block &g) {
     if (nv < 128) return true;
     if (wi == 4 ? taps == 8 && region > 1500 : region > 1300 || (nchunk <= 16 && region > 1024)) return true;
     if (wi == 16 && fi == 4) return nv < 32000 || (nv > 40000 && nv < (1 << 18) && uneven(g));
-    if (nv <= 8192) return d == 1;
-    return nv < 27000 || (nv <= 32768 && uneven(g)) || (wi == 4 && wd == 16 && nv <= (1 << 16));
+    if (wi == 4 && wd == 16) return nv > 6144 && nv <= (1 << 16);
+    if (nv <= 8192) return wi == 16 && d == 1;
+    return (wi == 16 && nv < (wd == 16 ? 27000 : 20000)) || (nv <= 32768 && uneven(g));
 }
 
 // The weight-gradient partials.
