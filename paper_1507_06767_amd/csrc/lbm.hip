@@ -571,42 +571,74 @@ void pair_once(lbm_blocks *h, int32_t sensor_every) {
 // as long as the workgroups fit the 256 compute units; so the tile is the one
 // with the least of that, times chunk + 2 planes (two are halo), times the
 // rounds of 256 workgroups.  (Lines written in part do not show on D3Q27,
-// whose planes are longer in arithmetic.)  Tiles of 64 x 8 columns take 1.25
-// times that (2048 x 32 x 32, 64 x 64 x 1000), ones of 64 x 9 do not; the tiles
-// next in line take as long there.
+// whose planes are longer in arithmetic.)
 //
 // float64 always pairs: of grids from 4^3 to 256^3, flat (1024 x 1024 x 4), long
 // (4 x 4 x 2000, 8 x 8 x 1024, 1000 x 10 x 10) and thin (5 x 400 x 400), none was
 // slower (us per step, one by one / in pairs: 24^3 10.5 / 9.4, 96^3 61.9 / 39.9,
 // 256^3 940 / 599, with Smagorinsky 64^3 22.8 / 22.6).
 //
-// float32 takes a pair where it is the shorter: its planes (longer with
-// Smagorinsky or a force, shorter without the sensor and in shifted storage)
-// and 5 us for its start and, with the sensor, the finishing launch, against
-// two steps one by one.  Those run at 6.8 TB/s plus 4 us (less in short steps)
-// while the single buffer of the in-place scheme stays in the 256 MB Infinity
-// Cache and at 5.3 TB/s above; with the sensor, slices of fewer than 32
-// workgroups add 3 ns per workgroup, as several slices of a block then meet at
-// its word (32 x 32 x 2048 48 us without the sensor, 86 with).  In the cache
-// the estimates are off by 5% and more and a wrong pair costs more than it
-// saves (it also touches both buffers), so that the estimate has to win by 5%
-// there, 3% without the sensor; the KKN sensor and a force weigh more there too,
-// where less time is spent waiting for memory.  Us per step, one by one / in
-// pairs, sensor at every step: D3Q19 float32 128^3 49.6 / 49.0 (not paired), with
-// the KKN sensor 52.5 / 59.1 (not paired), without a sensor 48.5 / 43.8; 160^3 116 / 97, 192^3 200 / 150, 256^3 439 / 324; 204 x 100 x 84
-// 43.1 / 43.6 (not paired), without the sensor 42.4 / 36.5, with a force 43.2 /
-// 45.0 (not paired); 64^3 without the sensor 6.9 / 9.8 (not paired); D3Q27 128^3
-// 70 / 83 (not paired), 192^3 286 / 226, 256^3 641 / 542.
+// float32 takes a pair where pair_us, two steps in one, is at least 4% less
+// than twice single_us; the two estimates are off by 6 to 10% (standard
+// deviation).  Of 869 runs measured both ways the rule pairs 318; 13 of
+// these are slower in pairs, by 4% at most, and all take 14% less in the mean.
+// Us per step, one by one / in pairs, D3Q19 float32: cavity 128^3 with the
+// sensor at every step 49.5 / 48.4, with the KKN sensor 51.5 / 58.5 (not paired),
+// without a sensor 49.0 / 43.2; 64^3 without a sensor 6.9 / 9.8 (not paired); 160^3
+// 116 / 97; 192^3 200 / 150; 256^3 439 / 324; 204 x 100 x 84 cavity 42.7 / 43.7 (not
+// paired), channel 42.4 / 35.0, with a force 43.5 / 42.1, that without a sensor 42.2
+// / 34.0; D3Q27 128^3 70 / 85 (not paired), 192^3 286 / 226, 256^3 641 / 542.
+
+// Estimated us of a pair on the tile p, of `best` us by the rule above, which
+// was fitted to cavities.  Where the state rests decides what bounds it:
+// buffers that both stay in the cache (up to 128 MiB), one that does, none.  The
+// less is spent waiting for memory, the more the arithmetic shows.
+double pair_us(const lbm_blocks *h, const PairArgs &p, double best, bool sensor) {
+    const lbm_desc &d = h->d;
+    const size_t mb = h->L.bytes[LBM_BUF_F_A] >> 20;
+    const int r = mb <= 128 ? 0 : (mb <= 240 ? 1 : 2);
+    constexpr double base[] = {0.78, 0.96, 0.92}, lid[] = {1.28, 1.14, 1.05}, force[] = {1.2, 1.13, 1.08};
+    constexpr double smag[] = {1.42, 1.24, 1.2}, kkn[] = {1.38, 1.21, 1.1}, wrap[] = {1.0, 1.04, 1.0};
+    double us = best * base[r];
+    if (p.W == 128) us *= 1.15;
+    if (p.W % 64 == 0 && p.H % 8 == 0) us *= 1.12;   // (64 x 9 columns do not show it)
+    // the workgroups at a moving wall take longest, unless their tile is cut short
+    const int rows = d.extent[1] - (p.nty - 1) * p.H;
+    if (p.moving & 15u)
+        us *= std::max(1.0, lid[r] * (p.moving & 7u ? 1.0 : (rows + 2.0) / (p.H + 2.0)));
+    if (!(h->wall_mask & 3u) && p.W % 32 == 0 && d.extent[0] > p.W) us *= wrap[r];
+    if (d.storage == LBM_F32_SHIFTED) us *= 0.97;
+    if (h->L.q == 27 && r > 0) us *= 1.12;
+    if (h->has_force) us *= force[r];
+    if (d.smagorinsky > 0.0) us *= smag[r] * (h->L.q == 27 ? 1.08 : 1.0);
+    if (!sensor) return 0.92 * us + 1.5;
+    return us * (d.sensor_kind == LBM_SENSOR_KKN ? kkn[r] : 1.0) + 5.0;   // its start and the finishing launch
+}
+
+// Estimated us of one step: 6.8 TB/s plus 4 us (less in short steps) in the
+// cache, 5.3 TB/s above; the KKN sensor adds 2.5 us, the other in slices of
+// fewer than 32 workgroups 3 ns per workgroup, as several slices of a block
+// then meet at its word (32 x 32 x 2048 48 us without the sensor, 86 with).
+double single_us(const lbm_blocks *h, bool cached, bool sensor) {
+    const lbm_desc &d = h->d;
+    const double us = (double)(2 * h->L.bytes[LBM_BUF_F_A]) / (cached ? 6.8e6 : 5.3e6);
+    if (!sensor) return us + std::min(4.0, 0.2 * us);
+    if (d.sensor_kind == LBM_SENSOR_KKN) return us + (cached ? 6.5 : 4.0);
+    const int slice = (d.extent[0] + h->tile_x - 1) / h->tile_x *
+                      ((d.extent[1] + tile_rows(h->tile_x) - 1) / tile_rows(h->tile_x));
+    return us + 4.0 + (h->inplace && slice < 32 ? 0.003 * slice * d.extent[2] * (1.0 - slice / 32.0) : 0.0);
+}
+
 void pair_setting(lbm_blocks *h) {
     const lbm_desc &d = h->d;
     const Layout &L = h->L;
-    const bool f64 = d.storage == LBM_F64, smag = d.smagorinsky > 0.0;
+    const bool f64 = d.storage == LBM_F64;
     h->pair_sensor = h->pair_plain = false;
     const char *env = std::getenv("LBM_PAIR");
     if (env && std::strcmp(env, "off") == 0) return;
     if (L.dim != 3 || d.storage > LBM_F32_SHIFTED) return;
     // as pair_supported
-    if (f64 ? d.lattice != LBM_D3Q19 || h->has_force : h->has_force && smag) return;
+    if (f64 ? d.lattice != LBM_D3Q19 || h->has_force : h->has_force && d.smagorinsky > 0.0) return;
     if (L.bytes[LBM_BUF_F_A] >= (size_t(1) << 32)) return;   // 32-bit byte offsets
     const int nx = d.extent[0], ny = d.extent[1], nz = d.extent[2];
     if (nx < 4 || ny < 4 || nz < 4) return;
@@ -650,19 +682,8 @@ void pair_setting(lbm_blocks *h) {
     h->pair_sensor = h->pair_plain = true;
     if (f64 || (env && std::strcmp(env, "on") == 0)) return;   // "on": tests and tuning
     const bool cached = h->inplace && L.bytes[LBM_BUF_F_A] <= (size_t(240) << 20);
-    if (p.W % 64 == 0 && p.H % 8 == 0) best *= 1.25;
-    if (d.storage == LBM_F32_SHIFTED) best *= 0.98;
-    if (L.q == 27) best *= 1.12;
-    if (smag) best *= L.q == 19 ? 1.2 : 1.3;
-    if (h->has_force) best *= cached ? 1.14 : 1.08;
-    const double with_sensor = best * (cached && d.sensor_kind == LBM_SENSOR_KKN ? 1.2 : 1.0) + 5.0;
-    const double bytes_us = (double)(2 * L.bytes[LBM_BUF_F_A]) / (cached ? 6.8e6 : 5.3e6);
-    double one_sensor = bytes_us + 4.0;
-    const int slice = (nx + h->tile_x - 1) / h->tile_x * ((ny + tile_rows(h->tile_x) - 1) / tile_rows(h->tile_x));
-    if (h->inplace && slice < 32) one_sensor += 0.003 * slice * nz * (1.0 - slice / 32.0);
-    const double one_plain = bytes_us + std::min(4.0, 0.2 * bytes_us);
-    h->pair_sensor = with_sensor < 2.0 * one_sensor * (cached ? 0.95 : 1.0);
-    h->pair_plain = 0.92 * best + 1.5 < 2.0 * one_plain * (cached ? 0.968 : 1.0);
+    h->pair_sensor = pair_us(h, p, best, true) < 0.96 * 2.0 * single_us(h, cached, true);
+    h->pair_plain = pair_us(h, p, best, false) < 0.96 * 2.0 * single_us(h, cached, false);
 }
 
 // Whether the two steps after `step` are to be one step_pair launch.
@@ -841,9 +862,9 @@ lbm_status lbm_create_blocks(const lbm_desc *d, const double *f0_host, lbm_block
     h->multi = (!h->inplace && multi_setting(d, L)) ? kMultiMaxSteps : 0;
     for (hipGraphExec_t &g : h->graph) g = nullptr;
     h->flip = 0;
-    pair_setting(h);
     for (int f = 0; f < 6; ++f)
         if (d->face_bc[f] == LBM_BC_WALL) h->wall_mask |= 1u << f;
+    pair_setting(h);
     h->flags_host.resize(L.nblocks);
     h->bmax_host.resize(L.nblocks * L.cbytes);
     hipError_t e = hipGetDevice(&h->device);
