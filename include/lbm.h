@@ -19,7 +19,7 @@
  *     lbm_required_bytes(), allocates them (for instance as torch tensors)
  *     and keeps them alive until lbm_destroy().  (Host data is read through
  *     pinned host memory, of which at most two rings of 16 MB and four pieces
- *     of 256 KB stay idle while there is a handle.)  The one exception is the
+ *     of 512 KB stay idle while there is a handle.)  The one exception is the
  *     32 KiB static workspace of lbm_conservation_noalloc, part of the
  *     library's code object.  Host arrays are only read or written during
  *     the call that receives them.
@@ -298,8 +298,9 @@ lbm_status lbm_conservation(lbm_blocks *h, double out[4]);
  * up once per device, on the first call there) instead of the handle's
  * scratch buffer.  No grid is too large for it: the first pass caps its
  * workgroups at 1024, each then summing more cells.  Allocates nothing and
- * calls no allocating routine; for an in-place handle the natural-order
- * copy of the state is built in F_B, which the caller already provided.
+ * calls no allocating routine; for an in-place handle that last took a
+ * gather-scatter step the natural-order copy of the state is built in F_B,
+ * which the caller already provided (else the state is read as it lies).
  * All calls on one GPU share the array: calls that overlap in time on one
  * GPU (two host threads, or two streams) race and must be serialised by the
  * caller.  Synchronises the stream. */

@@ -78,7 +78,8 @@ int32_t lbm_cnn_conv3d_wgrad_partials(const float *x, const float *gz, int32_t n
  * lbm_cnn_conv3d_forward(gz, ..., co, packed_flip, ci, NULL, 0, mask, gin)
  * (packed_flip from lbm_cnn_pack_weights with flip 1).  The same results as
  * those two calls, which it makes itself for shapes outside its fused forms
- * (4 or 16 padded channels each way, rows of a multiple of 4 voxels).  gz 16-
+ * (4 or 16 padded channels each way; rows of a multiple of 4 voxels, or x
+ * 16-byte aligned and rows of which a few fit local memory).  gz 16-
  * and packed_flip 8-byte aligned; -1 on a NULL pointer (mask may be NULL)
  * or a size < 1. */
 int32_t lbm_cnn_backward_layer(const float *x, const float *gz, int32_t n, int32_t d, int32_t h, int32_t wd,
